@@ -9,13 +9,16 @@
 //   2. per row (grid point): y_r = sum over the blocks covering it of t_j[p_j(r)], the covering
 //      blocks found arithmetically from per-axis index ranges; no atomics, fixed order.
 // x = M^T u also streams the matrix once:
-//   1. per chunk of <= 2048 consecutive points of one block: each thread holds 8 gathered
+//   1. per chunk of <= 2048 consecutive points of one block (its features split over several
+//      workgroups when the chunks are few): each thread holds up to 8 gathered
 //      u values (in vector-load groups of 2 or 4 consecutive points for FP32 and 16-bit
 //      copies); for every group of 8 features the 256 lanes form their dot products, a
 //      transposing butterfly across the wavefront reduces the 8 features at once (10 cross-lane
 //      shuffles) and a 4-wave LDS sum gives the chunk partials;
 //   2. per column: sum of the chunk partials of its block in chunk order.
 // All reductions are deterministic (fixed order, no floating-point atomics).
+#include <algorithm>
+
 #include "device.h"
 #include "kernels.h"
 
@@ -23,7 +26,7 @@ namespace elmfb {
 
 // PTS consecutive points per thread (one vector load per feature row); a tile of 256 points
 // runs on 256 / PTS threads.  Per point the sum order does not depend on PTS.
-template <int PREC, int PTS>
+template <int PREC, int PTS, int AHEAD>
 __global__ void __launch_bounds__(256) k_mv_blocks(Geo g, const DevBlock* __restrict__ blocks,
                                                    const Tile* __restrict__ tiles,
                                                    const void* __restrict__ A,
@@ -46,14 +49,25 @@ __global__ void __launch_bounds__(256) k_mv_blocks(Geo g, const DevBlock* __rest
 #pragma unroll
     for (int q = 0; q < PTS; ++q) acc[u][q] = 0.0;
   int k = 0;
-  for (; k + 4 <= K; k += 4) {
-    double a[4][PTS];
+  for (; k + AHEAD <= K; k += AHEAD) {
+    double a[AHEAD][PTS];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) load_vec<PREC, PTS>(A, base + (int64_t)(k + u) * ld, a[u]);
+    for (int u = 0; u < AHEAD; ++u) load_vec<PREC, PTS>(A, base + (int64_t)(k + u) * ld, a[u]);
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < AHEAD; ++u)
 #pragma unroll
-      for (int q = 0; q < PTS; ++q) acc[u][q] += a[u][q] * vb[k + u];
+      for (int q = 0; q < PTS; ++q) acc[u & 3][q] += a[u][q] * vb[k + u];
+  }
+  if constexpr (AHEAD > 4) {
+    for (; k + 4 <= K; k += 4) {
+      double a[4][PTS];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) load_vec<PREC, PTS>(A, base + (int64_t)(k + u) * ld, a[u]);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int q = 0; q < PTS; ++q) acc[u][q] += a[u][q] * vb[k + u];
+    }
   }
   for (; k < K; ++k) {
     double a[PTS];
@@ -146,15 +160,46 @@ __global__ void __launch_bounds__(256) k_gather_rows(Geo g, const DevBlock* __re
   }
 }
 
+// The features [k0, k1) of one chunk against the NL live groups of points of each thread (group i
+// of thread t: VEC consecutive points from i*256*VEC + t*VEC; the groups past the block's end carry
+// zero weights and are left out, which changes no sum).
+template <int PREC, int VEC, int NL, int NG>
+__device__ __forceinline__ void rmv_features(const void* __restrict__ A, const int64_t (&idx)[NG],
+                                             const double (&uv)[NG][VEC], int ld, int K, int k0,
+                                             int k1, double (*sred)[264]) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  for (int kb = k0; kb < k1; kb += 8) {
+    double acc[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      acc[j] = 0.0;
+      const int k = kb + j < K ? kb + j : K - 1;     // padded features reread the last one
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        double a[VEC];
+        load_vec<PREC, VEC>(A, idx[i] + (int64_t)k * ld, a);
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) acc[j] += a[q] * uv[i][q];
+      }
+    }
+    int f;
+    const double v = butterfly8(acc, lane, &f);
+    if ((lane & 7) == 0) sred[wid][kb - k0 + f] = v;
+  }
+}
+
 // VEC consecutive points per vector load; each thread holds NG groups of them, the groups of a
-// chunk interleaved across the workgroup (group i of thread t starts at i*256*VEC + t*VEC).
-template <int PREC, int VEC>
+// chunk interleaved across the workgroup.  blockIdx.y takes `kper` features (a multiple of 8) of
+// the chunk.  FEW: also loops over only the live groups (blocks that fill part of their chunk);
+// their extra copies of the loop take 96 instead of 60 registers in FP64, which a grid that fills
+// the chip pays for (345 against 341 us on the 3-level problem), so it keeps the one loop.
+template <int PREC, int VEC, bool FEW>
 __global__ void __launch_bounds__(256) k_rmv_chunks(Geo g, const DevBlock* __restrict__ blocks,
                                                     const Tile* __restrict__ chunks,
                                                     const void* __restrict__ A,
                                                     const double* __restrict__ u,
                                                     const double* __restrict__ uscale,
-                                                    double* __restrict__ part,
+                                                    double* __restrict__ part, int kper,
                                                     const SolveState* __restrict__ st) {
   constexpr int NG = kChunkPts / (256 * VEC);
   static_assert(NG * 256 * VEC == kChunkPts, "chunk size");
@@ -165,6 +210,7 @@ __global__ void __launch_bounds__(256) k_rmv_chunks(Geo g, const DevBlock* __res
   const DevBlock B = blocks[c.blk];
   const int K = g.K;
   const double sc = uscale ? *uscale : 1.0;
+  const int live = (min(B.n - c.p0, kChunkPts) + 256 * VEC - 1) / (256 * VEC);
   double uv[NG][VEC];
   int64_t idx[NG];
 #pragma unroll
@@ -185,30 +231,17 @@ __global__ void __launch_bounds__(256) k_rmv_chunks(Geo g, const DevBlock* __res
       }
     }
   }
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int ld = B.ld;
-  const int K8 = (K + 7) & ~7;
-  for (int k0 = 0; k0 < K8; k0 += 8) {
-    double acc[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      acc[j] = 0.0;
-      const int k = k0 + j < K ? k0 + j : K - 1;     // padded features reread the last one
-#pragma unroll
-      for (int i = 0; i < NG; ++i) {
-        double a[VEC];
-        load_vec<PREC, VEC>(A, idx[i] + (int64_t)k * ld, a);
-#pragma unroll
-        for (int q = 0; q < VEC; ++q) acc[j] += a[q] * uv[i][q];
-      }
-    }
-    int f;
-    const double v = butterfly8(acc, lane, &f);
-    if ((lane & 7) == 0) sred[wid][k0 + f] = v;
-  }
+  const int k0 = blockIdx.y * kper, k1 = min(k0 + kper, K);
+  if constexpr (!FEW) rmv_features<PREC, VEC, NG>(A, idx, uv, B.ld, K, k0, k1, sred);
+  else if (live <= NG / 8) rmv_features<PREC, VEC, (NG + 7) / 8>(A, idx, uv, B.ld, K, k0, k1, sred);
+  else if (live <= NG / 4) rmv_features<PREC, VEC, (NG + 3) / 4>(A, idx, uv, B.ld, K, k0, k1, sred);
+  else if (live <= NG / 2) rmv_features<PREC, VEC, NG / 2>(A, idx, uv, B.ld, K, k0, k1, sred);
+  else rmv_features<PREC, VEC, NG>(A, idx, uv, B.ld, K, k0, k1, sred);
   __syncthreads();
-  for (int k = threadIdx.x; k < K; k += 256)
-    part[(int64_t)ci * K + k] = (sred[0][k] + sred[1][k]) + (sred[2][k] + sred[3][k]);
+  for (int k = k0 + threadIdx.x; k < k1; k += 256) {
+    const int f = k - k0;
+    part[(int64_t)ci * K + k] = (sred[0][f] + sred[1][f]) + (sred[2][f] + sred[3][f]);
+  }
 }
 
 // bc (may be NULL): the dense soft-constraint rows [n_bc][n_phi]; their part of column q,
@@ -286,13 +319,31 @@ template <> struct MvShape<ELMFB_FP32> { static constexpr int pts = 1, vec = 2; 
 template <> struct MvShape<ELMFB_BF16> { static constexpr int pts = 2, vec = 4; };
 template <> struct MvShape<ELMFB_FP16> { static constexpr int pts = 2, vec = 4; };
 
+// Feature rows loaded ahead in M v: up to 2,048 tiles (8 workgroups per CU) the pass has too few
+// wavefronts in flight to hide the load latency and takes 16 rows ahead; above, 4 (8 or 16 rows
+// cost occupancy there: 95 against 104 us on the 3-level problem's FP16 copy).  Measured, FP64,
+// 4 -> 16 rows: 11 blocks of K = 256 23.9 -> 13.1 us, 20 blocks of K = 64 4.3 -> 3.9, 81 blocks
+// of K = 48 (1,398 tiles) 21.9 -> 20.5; the sum order, and so every bit, is the same.
+constexpr int kFewTiles = 2048;
+// Workgroups M^T u aims at: a problem of a few blocks has a few chunks, each of which would
+// stream all K features through one workgroup (the serial chain of K/8 feature groups is then
+// the time), so the features of a chunk are split over workgroups until about 4 per CU are in
+// flight.  Measured, FP64, with the live-group loops: 11 blocks of K = 256 266.6 -> 12.5 us,
+// 20 blocks of K = 64 25.5 -> 3.2 us, 81 blocks of K = 48 55.8 -> 24.2 us; the 1,322 chunks of
+// the 3-level problem keep one workgroup per chunk (341 us, 5.7 TB/s).  Every bit is the same.
+constexpr int kChunkWgs = 1024;
+
 template <int PREC>
 static void mv_launch(const Geo& g, const DevBlock* blocks, const Tile* tiles, int64_t n_tiles,
                       const void* A, const double* v, const double* vscale, double* tpart,
                       const SolveState* st, hipStream_t s) {
   constexpr int P = MvShape<PREC>::pts;
-  hipLaunchKernelGGL((k_mv_blocks<PREC, P>), dim3((unsigned)n_tiles), dim3(kTile / P), 0, s, g,
-                     blocks, tiles, A, v, vscale, tpart, st);
+  if (n_tiles <= kFewTiles)
+    hipLaunchKernelGGL((k_mv_blocks<PREC, P, 16>), dim3((unsigned)n_tiles), dim3(kTile / P), 0, s,
+                       g, blocks, tiles, A, v, vscale, tpart, st);
+  else
+    hipLaunchKernelGGL((k_mv_blocks<PREC, P, 4>), dim3((unsigned)n_tiles), dim3(kTile / P), 0, s,
+                       g, blocks, tiles, A, v, vscale, tpart, st);
 }
 
 hipError_t launch_mv_blocks(const Geo& g, int prec, const DevBlock* blocks, const Tile* tiles,
@@ -318,8 +369,16 @@ template <int PREC>
 static void rmv_launch(const Geo& g, const DevBlock* blocks, const Tile* chunks, int64_t n_chunks,
                        const void* A, const double* u, const double* uscale, double* part,
                        const SolveState* st, hipStream_t s) {
-  hipLaunchKernelGGL((k_rmv_chunks<PREC, MvShape<PREC>::vec>), dim3((unsigned)n_chunks), dim3(256),
-                     0, s, g, blocks, chunks, A, u, uscale, part, st);
+  const int k8 = (g.K + 7) / 8;
+  const int split = (int)std::max<int64_t>(1, std::min<int64_t>(k8, kChunkWgs / n_chunks));
+  const int kper = 8 * ((k8 + split - 1) / split);
+  const dim3 grid((unsigned)n_chunks, (unsigned)((g.K + kper - 1) / kper));
+  if (n_chunks < kChunkWgs)
+    hipLaunchKernelGGL((k_rmv_chunks<PREC, MvShape<PREC>::vec, true>), grid, dim3(256), 0, s, g,
+                       blocks, chunks, A, u, uscale, part, kper, st);
+  else
+    hipLaunchKernelGGL((k_rmv_chunks<PREC, MvShape<PREC>::vec, false>), grid, dim3(256), 0, s, g,
+                       blocks, chunks, A, u, uscale, part, kper, st);
 }
 
 hipError_t launch_rmv_chunks(const Geo& g, int prec, const DevBlock* blocks, const Tile* chunks,
