@@ -65,24 +65,21 @@ __device__ inline void axis_segment_entries(const Geo& g, const AxisSeg& sg,
 }
 
 // The K features of the block whose first column is q0, staged for the entry loop (strided over
-// the workgroup's threads): w = (W1, W2) and b as given, c = (W1/s_x, W2/s_y) with s the feature
-// input scale of level l (the chain-rule factor of d/dx tanh(W xbar + b)), and c3 = |c|^2.
+// the workgroup's threads) in pairs that one 16-byte LDS read fetches: w = (W1, W2) as given,
+// c = (W1/s_x, W2/s_y) with s the feature input scale of level l (the chain-rule factor of
+// d/dx tanh(W xbar + b)), and b = (bias, |c|^2).
 __device__ inline void stage_block_features(const Geo& g, int l, int64_t q0, int K,
                                             const double* __restrict__ W,
-                                            const double* __restrict__ bias, double* w1s,
-                                            double* w2s, double* c1s, double* c2s, double* c3s,
-                                            double* bs) {
+                                            const double* __restrict__ bias, double2* ws,
+                                            double2* cs, double2* bs) {
   const double sx = feat_div(g, l, 0), sy = feat_div(g, l, 1);
   for (int k = threadIdx.x; k < K; k += blockDim.x) {
     const double w1 = W[2 * (q0 + k)];
     const double w2 = (g.dim == 2) ? W[2 * (q0 + k) + 1] : 0.0;
     const double c1 = w1 / sx, c2 = (g.dim == 2) ? w2 / sy : 0.0;
-    w1s[k] = w1;
-    w2s[k] = w2;
-    c1s[k] = c1;
-    c2s[k] = c2;
-    c3s[k] = c1 * c1 + c2 * c2;
-    bs[k] = bias[q0 + k];
+    ws[k] = double2{w1, w2};
+    cs[k] = double2{c1, c2};
+    bs[k] = double2{bias[q0 + k], c1 * c1 + c2 * c2};
   }
 }
 
@@ -116,13 +113,31 @@ template <>
 __device__ __forceinline__ void store_entry<ELMFB_FP32>(void* A, int64_t i, double v) {
   static_cast<float*>(A)[i] = (float)v;
 }
+// The 16-bit stores round to odd at 24 bits first (the dropped bits or'ed into the last kept one),
+// which FP32 holds exactly: the second rounding then sees which side of every tie the FP64 value
+// lies on, so the result is the single rounding of f64_to_*_rne in a few instructions.
+__device__ __forceinline__ float round_to_odd_f32(double v) {
+  const uint64_t u = __double_as_longlong(v);
+  const uint64_t odd = (u & 0x1fffffffull) ? 0x20000000ull : 0;
+  float f = (float)__longlong_as_double((long long)((u & ~0x1fffffffull) | odd));
+  asm("" : "+v"(f));   // else the two conversions are merged into a 35-instruction FP64 to FP16
+  return f;
+}
 template <>
 __device__ __forceinline__ void store_entry<ELMFB_BF16>(void* A, int64_t i, double v) {
-  static_cast<uint16_t*>(A)[i] = f64_to_bf16_rne(v);
+  uint16_t r;
+  if (fabs(v) >= 0x1p-120) {     // FP32 normals; smaller values (and NaN) by the general rounding
+    const uint32_t u = __float_as_uint(round_to_odd_f32(v));
+    r = (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
+  } else {
+    r = f64_to_bf16_rne(v);
+  }
+  static_cast<uint16_t*>(A)[i] = r;
 }
 template <>
 __device__ __forceinline__ void store_entry<ELMFB_FP16>(void* A, int64_t i, double v) {
-  static_cast<uint16_t*>(A)[i] = f64_to_fp16_rne(v);
+  // FP16's smallest spacing is 2^-24: what FP32 flushes on the way rounds to zero in any case
+  static_cast<_Float16*>(A)[i] = (_Float16)round_to_odd_f32(v);
 }
 
 }  // namespace elmfb

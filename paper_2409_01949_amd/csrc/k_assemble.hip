@@ -18,6 +18,7 @@
 // wavefront writes 64 consecutive points of one feature.
 #include "device.h"
 #include "envelope.h"
+#include "fast_tanh.h"
 #include "kernels.h"
 
 namespace elmfb {
@@ -91,6 +92,12 @@ __device__ __forceinline__ void l_envelope(const Geo& g, int l, int ix, int iy, 
 
 // One workgroup per tile of <= 256 points of one block; one thread per point, looping over K.
 // LO < 0: FP64 matrix only; LO = FP32 / BF16 / FP16: also its rounded copy.
+// Bound by instruction issue: 46 FP64 and about 30 other instructions an entry (25 of them the
+// tanh, 10 the operator; the 16-bit rounding 8).  The FP64 entries are streamed out (non-temporal:
+// the next pass over gigabytes finds nothing of them in the caches), the narrow copy is not (its
+// 2-byte lanes need the caches to merge lines: 719 us with the hint).  3-level problem with FP16
+// copy, 242e6 entries, 2.42 GB written: 1,775 us with the device library's tanh, 753 with the
+// table, 643 with the short rounding, 550 with streamed stores (4.4 TB/s).
 template <int LO, int OP>
 __global__ void __launch_bounds__(256) k_assemble(Geo g, const DevBlock* __restrict__ blocks,
                                                   const Tile* __restrict__ tiles,
@@ -99,12 +106,14 @@ __global__ void __launch_bounds__(256) k_assemble(Geo g, const DevBlock* __restr
                                                   const double* __restrict__ bias,
                                                   double* __restrict__ A,
                                                   void* __restrict__ A_lo) {
-  __shared__ double w1s[256], w2s[256], c1s[256], c2s[256], c3s[256], bs[256];
+  __shared__ double2 tt[kTanhN];
+  __shared__ double2 ws[256], cs[256], bs[256];
   const Tile t = tiles[blockIdx.x];
   const DevBlock B = blocks[t.blk];
   const int K = g.K;
   const int l = B.level;
-  stage_block_features(g, l, B.q0, K, W, bias, w1s, w2s, c1s, c2s, c3s, bs);
+  stage_tanh(tt);
+  stage_block_features(g, l, B.q0, K, W, bias, ws, cs, bs);
   __syncthreads();
   const int p = t.p0 + threadIdx.x;
   if (p >= B.n) return;
@@ -124,6 +133,7 @@ __global__ void __launch_bounds__(256) k_assemble(Geo g, const DevBlock* __restr
     Py = X0 * Y1;
     LP = X2 * Y0 + X0 * Y2;
   }
+  if (outside) P = Px = Py = LP = 0.0;   // zero rows
   // feature inputs: subdomain-local (x - mu)/sigma, or x with global inputs
   const int jx = B.jx, jy = B.jy;
   const double xb = feat_in(g, l, 0, jx, grid_coord(g, 0, B.ix0 + lx));
@@ -132,12 +142,13 @@ __global__ void __launch_bounds__(256) k_assemble(Geo g, const DevBlock* __restr
   const int64_t base = B.a_off + p;
   const int ld = B.ld;
   for (int k = 0; k < K; ++k) {
-    const double z = w1s[k] * xb + w2s[k] * yb + bs[k];
-    const double ph = tanh(z);
+    const double2 w = ws[k], c = cs[k], b = bs[k];
+    const double z = w.x * xb + w.y * yb + b.x;
+    const double ph = table_tanh(z, tt);
     const double sd = 1.0 - ph * ph;
-    const double v = operator_entry(OP, g.op_coef, P, Px, Py, LP, ph, sd, c1s[k], c2s[k], c3s[k]);
-    const double e = outside ? 0.0 : v * scale;
-    A[base + (int64_t)k * ld] = e;
+    const double v = operator_entry(OP, g.op_coef, P, Px, Py, LP, ph, sd, c.x, c.y, b.y);
+    const double e = v * scale;
+    __builtin_nontemporal_store(e, A + base + (int64_t)k * ld);
     if constexpr (LO >= 0) store_entry<LO>(A_lo, base + (int64_t)k * ld, e);
   }
 }
