@@ -959,15 +959,17 @@ elmfb_status elmfb_batch_precondition_patches(elmfb_batch B, double shift, int32
         return bfail(B, ELMFB_E_NOMEM, std::string("factor storage: ") + hipGetErrorString(e2));
       }
     }
-    double* G = nullptr;
+    double *G = nullptr, *Wk = nullptr;
     hipError_t e1 = balloc(B, &G, B->n_gsq * 8);
+    if (e1 == hipSuccess) e1 = balloc(B, &Wk, B->n_gsq * 8);
+    if (e1 != hipSuccess) bfree(B, G);
     if (e1 != hipSuccess)
       return bfail(B, ELMFB_E_NOMEM, std::string("Gram scratch: ") + hipGetErrorString(e1));
     if (e == hipSuccess)
       e = launch_bt_gram_diag(B->d_blocks, B->d_tasks, nb, false, B->d_A, B->d_goff, G, s);
     if (e == hipSuccess)
-      e = launch_bt_bj_factor(B->d_blocks, 0, nb, G, B->d_goff, B->d_foff, B->kmax, shift, B->d_rc,
-                              B->d_flag, s);
+      e = launch_bt_bj_factor(B->d_blocks, 0, nb, B->kmax, G, Wk, B->d_goff, B->d_foff, shift,
+                              B->d_rc, B->d_flag, s);
     // M R^{-1} in FP64, and its rounded copy in place of the low-precision M
     if (e == hipSuccess)
       e = launch_bt_fold(B->lo_prec, false, B->kmax, B->d_blocks, B->d_ftiles,
@@ -976,6 +978,7 @@ elmfb_status elmfb_batch_precondition_patches(elmfb_batch B, double shift, int32
     if (e == hipSuccess) e = hipMemcpyAsync(&nfail, B->d_flag, 4, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     bfree(B, G);
+    bfree(B, Wk);
     BHIP(B, e);
     B->lo_hat = B->lo_prec != ELMFB_FP64;
   } else {
@@ -1030,7 +1033,7 @@ elmfb_status elmfb_batch_precondition_patches(elmfb_batch B, double shift, int32
     }
     double *G = nullptr, *Wk = nullptr;
     hipError_t e1 = balloc(B, &G, B->pn_scratch * 8);
-    if (e1 == hipSuccess && B->pkmax > kBatchMaxK) e1 = balloc(B, &Wk, B->pn_scratch * 8);
+    if (e1 == hipSuccess) e1 = balloc(B, &Wk, B->pn_scratch * 8);
     if (e1 != hipSuccess) {
       bfree(B, G);
       return bfail(B, ELMFB_E_NOMEM, std::string("patch Gram scratch: ") + hipGetErrorString(e1));
@@ -1044,14 +1047,9 @@ elmfb_status elmfb_batch_precondition_patches(elmfb_batch B, double shift, int32
       const int64_t t0 = B->pchunk_task[c], t1 = B->pchunk_task[c + 1];
       e = launch_bt_gram_diag(B->d_pblocks, B->d_ptasks + t0, t1 - t0, B->pkmax > kBatchMaxK,
                               B->d_pAhat, B->d_pgoff, G, s);
-      if (e == hipSuccess) {
-        if (B->pkmax <= kBatchMaxK)
-          e = launch_bt_bj_factor(B->d_pblocks, (int)b0, b1 - b0, G, B->d_pgoff, B->d_pfoff,
-                                  B->pkmax, shift, B->d_prc, B->d_flag, s);
-        else
-          e = launch_bt_bj_factor_blocked(B->d_pblocks, (int)b0, b1 - b0, G, Wk, B->d_pgoff,
-                                          B->d_pfoff, shift, B->d_prc, B->d_flag, s);
-      }
+      if (e == hipSuccess)
+        e = launch_bt_bj_factor(B->d_pblocks, (int)b0, b1 - b0, B->pkmax, G, Wk, B->d_pgoff,
+                                B->d_pfoff, shift, B->d_prc, B->d_flag, s);
     }
     if (e == hipSuccess)
       e = launch_bt_fold(B->lo_prec, false, B->pkmax, B->d_pblocks, B->d_pftiles,

@@ -1,7 +1,7 @@
 // Block-Jacobi preconditioning for batches: per subdomain block b (K_b <= 128 features) the
 // diagonal Gram block G_b = M_b^T M_b on the matrix cores, the upper Cholesky factor R_b of
-// G_b + lambda_b I (lambda_b = shift trace(G_b)/K_b) and its inverse (column-packed), then the
-// preconditioned matrix M_b R_b^{-1} formed once on the matrix cores, so that preconditioned
+// G_b + lambda_b I (lambda_b = shift trace(G_b)/K_b) and its inverse (column-packed; k_factor.hip),
+// then the preconditioned matrix M_b R_b^{-1} formed once on the matrix cores, so that preconditioned
 // Krylov steps cost the same as plain ones.  Same preconditioner as for single problems (the
 // random features of one subdomain are the main source of the condition numbers of M, Sec. 5),
 // with the ragged K of the instances.
@@ -85,112 +85,6 @@ __global__ void __launch_bounds__(256) k_bt_gram_diag(const DevBlock* __restrict
       }
     }
   }
-}
-
-// Blocks of at most 128 columns: one workgroup of 1,024 threads per block (blocks blk0 + workgroup
-// index), everything in LDS (two packed upper triangles of
-// K(K+1)/2 doubles, (i, j) at j(j+1)/2 + i, and one row vector): the upper Cholesky factor R of
-// G_b + lambda I by right-looking elimination (step k: the pivot row R[k][j] = G'[k][j] / sqrt of
-// the pivot, kept in the row vector, then the trailing update R[i][j] -= R[k][i] R[k][j] for
-// k < i <= j), then X = R^{-1} by the same elimination from the bottom row (row i of X is row i of
-// the running right-hand side over R[i][i]; rows r < i then lose R[r][i] X[i][j]), written out in
-// the same column-packed layout.  Each update is spread as 8 threads per column j over its rows,
-// which are contiguous in the packed layout, so a thread's updates are independent of each
-// other.  A failed factorisation is retried with a 100x larger shift up to 8 times; after that,
-// or for an all-zero block, the block gets the identity and nfail counts it.
-constexpr int kFacThreads = 1024;
-
-__global__ void __launch_bounds__(kFacThreads) k_bt_bj_factor(const DevBlock* __restrict__ blocks,
-                                                              int blk0,
-                                                              const double* __restrict__ G,
-                                                              const int64_t* __restrict__ goff,
-                                                              const int64_t* __restrict__ foff,
-                                                              double shift,
-                                                              double* __restrict__ rc,
-                                                              int32_t* __restrict__ nfail) {
-  extern __shared__ double lds[];
-  __shared__ double part[kFacThreads / 64];
-  __shared__ double row[kBatchMaxK];
-  const int b = blk0 + (int)blockIdx.x;
-  const DevBlock B = blocks[b];
-  const int K = B.nk;
-  const int np = K * (K + 1) / 2;
-  double* Rp = lds;
-  double* Xp = lds + np;
-  const double* Gj = G + goff[b];
-  double* Pc = rc + foff[b];
-  const int t = threadIdx.x, tc = t >> 3, ts = t & 7;   // column offset, row phase
-  // trace of G_b
-  double tr = 0.0;
-  for (int i = t; i < K; i += kFacThreads) tr += Gj[(int64_t)i * K + i];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) tr += __shfl_xor(tr, o);
-  if ((t & 63) == 0) part[t >> 6] = tr;
-  __syncthreads();
-  tr = 0.0;
-  for (int w = 0; w < kFacThreads / 64; ++w) tr += part[w];
-  double lam = shift * tr / K;
-  bool ok = lam > 0.0;
-  bool bad = true;
-  for (int attempt = 0; attempt < 8 && ok; ++attempt) {
-    for (int e = t; e < K * K; e += kFacThreads) {
-      const int i = e / K, j = e - (e / K) * K;
-      if (i <= j) Rp[j * (j + 1) / 2 + i] = Gj[e] + (i == j ? lam : 0.0);
-    }
-    __syncthreads();
-    bad = false;
-    for (int k = 0; k < K; ++k) {
-      const double d = Rp[k * (k + 1) / 2 + k];
-      if (!(d > 0.0)) { bad = true; break; }    // every thread reads the same value
-      const double rk = sqrt(d);
-      for (int j = k + 1 + t; j < K; j += kFacThreads) {
-        const double v = Rp[j * (j + 1) / 2 + k] / rk;
-        Rp[j * (j + 1) / 2 + k] = v;
-        row[j] = v;
-      }
-      __syncthreads();
-      if (t == 0) Rp[k * (k + 1) / 2 + k] = rk;
-      const int j = k + 1 + tc;
-      if (j < K) {
-        double* cj = Rp + j * (j + 1) / 2;
-        const double rkj = row[j];
-        for (int i = k + 1 + ts; i <= j; i += 8) cj[i] -= row[i] * rkj;
-      }
-      __syncthreads();
-    }
-    if (!bad) break;
-    __syncthreads();
-    lam *= 100.0;
-    ok = attempt < 7;
-  }
-  if (bad) {
-    if (t == 0) atomicAdd(nfail, 1);
-    for (int e = t; e < np; e += kFacThreads) Pc[e] = 0.0;
-    for (int i = t; i < K; i += kFacThreads) Pc[i * (i + 1) / 2 + i] = 1.0;
-    return;
-  }
-  for (int e = t; e < np; e += kFacThreads) Xp[e] = 0.0;
-  __syncthreads();
-  for (int i = t; i < K; i += kFacThreads) Xp[i * (i + 1) / 2 + i] = 1.0;
-  __syncthreads();
-  for (int i = K - 1; i >= 0; --i) {
-    const int ci = i * (i + 1) / 2;
-    const double rii = Rp[ci + i];
-    for (int j = i + t; j < K; j += kFacThreads) {
-      const double v = Xp[j * (j + 1) / 2 + i] / rii;
-      Xp[j * (j + 1) / 2 + i] = v;
-      row[j] = v;
-    }
-    __syncthreads();
-    const int j = i + tc;
-    if (j < K) {
-      double* xj = Xp + j * (j + 1) / 2;
-      const double xij = row[j];
-      for (int r = ts; r < i; r += 8) xj[r] -= Rp[ci + r] * xij;
-    }
-    __syncthreads();
-  }
-  for (int e = t; e < np; e += kFacThreads) Pc[e] = Xp[e];
 }
 
 // Fold the preconditioner into the matrix: Mhat_b = M_b R_b^{-1}, i.e. in the feature-major
@@ -311,162 +205,6 @@ hipError_t launch_bt_fold(int lo_prec, bool full, int kmax, const DevBlock* bloc
   return hipGetLastError();
 }
 
-// Blocks of up to kPatchMaxK columns (the patches of P^d neighbouring subdomains): one workgroup
-// of 256 threads per block (blocks blk0 + workgroup index), the matrices in global memory, nk x nk
-// row-major at goff[b] in W (the factor) and G (the Gram block, then the inverse), panels of 16
-// rows in LDS.  Cholesky R^T R = G_b + lambda I by right-looking block elimination: per panel the
-// 16 x 16 diagonal block is factorised in LDS, the panel rows R[kb.., kb+16..] = R_kk^{-T} W[..]
-// are solved one column per thread, and the trailing upper triangle loses Pn^T Pn.  Then
-// X = R^{-1} block row by block row from the bottom: for column j,
-// X[I, j] = R_II^{-1} (e_j - sum_{s > I} R[I, s] X[s, j]), with the block row of R in LDS and the
-// rows of X below it read back from G.  X goes out column-packed at foff[b].  A failed
-// factorisation is retried with a 100x larger shift up to 8 times; after that, or for an all-zero
-// block, the block gets the identity and nfail counts it.
-constexpr int kPanel = 16;
-constexpr int kRows = 8;   // rows of a trailing update in flight per thread
-
-__global__ void __launch_bounds__(256) k_bt_bj_factor_blocked(const DevBlock* __restrict__ blocks,
-                                                              int blk0, double* __restrict__ G,
-                                                              double* __restrict__ W,
-                                                              const int64_t* __restrict__ goff,
-                                                              const int64_t* __restrict__ foff,
-                                                              double shift,
-                                                              double* __restrict__ rc,
-                                                              int32_t* __restrict__ nfail) {
-  __shared__ double Pn[kPanel][kPatchMaxK];
-  __shared__ double D[kPanel][kPanel + 1];
-  __shared__ double part[4];
-  const int b = blk0 + (int)blockIdx.x;
-  const DevBlock B = blocks[b];
-  const int K = B.nk;
-  double* Gb = G + goff[b];
-  double* Wb = W + goff[b];
-  double* Pc = rc + foff[b];
-  const int t = threadIdx.x;
-  double tr = 0.0;
-  for (int i = t; i < K; i += 256) tr += Gb[(int64_t)i * K + i];
-  tr = wave_sum(tr);
-  if ((t & 63) == 0) part[t >> 6] = tr;
-  __syncthreads();
-  tr = (part[0] + part[1]) + (part[2] + part[3]);
-  double lam = shift * tr / K;
-  bool ok = lam > 0.0;
-  bool bad = true;
-  for (int attempt = 0; attempt < 8 && ok; ++attempt) {
-    __syncthreads();
-    for (int64_t e = t; e < (int64_t)K * K; e += 256) {
-      const int i = (int)(e / K), j = (int)(e - (int64_t)i * K);
-      if (i <= j) Wb[e] = Gb[e] + (i == j ? lam : 0.0);
-    }
-    __syncthreads();
-    bad = false;
-    for (int kb = 0; kb < K; kb += kPanel) {
-      const int nb = min(kPanel, K - kb);
-      const int r16 = t >> 4, c16 = t & 15;
-      if (r16 < nb && c16 < nb) D[r16][c16] = r16 <= c16 ? Wb[(int64_t)(kb + r16) * K + kb + c16] : 0.0;
-      __syncthreads();
-      for (int k = 0; k < nb; ++k) {
-        const double d = D[k][k];      // the same value in every thread
-        if (!(d > 0.0)) { bad = true; break; }
-        const double rk = sqrt(d);
-        __syncthreads();
-        if (t > k && t < nb) D[k][t] /= rk;
-        if (t == 0) D[k][k] = rk;
-        __syncthreads();
-        if (r16 > k && r16 < nb && c16 >= r16 && c16 < nb) D[r16][c16] -= D[k][r16] * D[k][c16];
-        __syncthreads();
-      }
-      if (bad) break;
-      if (r16 < nb && c16 < nb && r16 <= c16) Wb[(int64_t)(kb + r16) * K + kb + c16] = D[r16][c16];
-      const int j0 = kb + nb;
-      for (int j = j0 + t; j < K; j += 256) {
-        double p[kPanel];
-#pragma unroll
-        for (int r = 0; r < kPanel; ++r) {
-          if (r < nb) {
-            double v = Wb[(int64_t)(kb + r) * K + j];
-#pragma unroll
-            for (int q = 0; q < r; ++q) v -= D[q][r] * p[q];
-            p[r] = v / D[r][r];
-            Pn[r][j] = p[r];
-            Wb[(int64_t)(kb + r) * K + j] = p[r];
-          }
-        }
-      }
-      __syncthreads();
-      // trailing update, kRows rows at a time so that their loads are in flight together
-      for (int i0 = j0; i0 < K; i0 += kRows) {
-        for (int j = i0 + t; j < K; j += 256) {
-          double pj[kPanel], w[kRows];
-#pragma unroll
-          for (int r = 0; r < kPanel; ++r) pj[r] = r < nb ? Pn[r][j] : 0.0;
-#pragma unroll
-          for (int a = 0; a < kRows; ++a)
-            w[a] = i0 + a <= j ? Wb[(int64_t)(i0 + a) * K + j] : 0.0;
-#pragma unroll
-          for (int a = 0; a < kRows; ++a) {
-            if (i0 + a <= j) {
-#pragma unroll
-              for (int r = 0; r < kPanel; ++r)
-                if (r < nb) w[a] -= Pn[r][i0 + a] * pj[r];
-              Wb[(int64_t)(i0 + a) * K + j] = w[a];
-            }
-          }
-        }
-      }
-      __syncthreads();
-    }
-    if (!bad) break;
-    lam *= 100.0;
-    ok = attempt < 7;
-  }
-  if (bad) {
-    if (t == 0) atomicAdd(nfail, 1);
-    for (int64_t e = t; e < (int64_t)K * (K + 1) / 2; e += 256) Pc[e] = 0.0;
-    for (int i = t; i < K; i += 256) Pc[(int64_t)i * (i + 1) / 2 + i] = 1.0;
-    return;
-  }
-  __syncthreads();
-  for (int ib = ((K - 1) / kPanel) * kPanel; ib >= 0; ib -= kPanel) {
-    const int nb = min(kPanel, K - ib);
-    for (int e = t; e < nb * (K - ib); e += 256) {
-      const int r = e / (K - ib), c = ib + (e - (e / (K - ib)) * (K - ib));
-      Pn[r][c] = Wb[(int64_t)(ib + r) * K + c];
-    }
-    __syncthreads();
-    for (int j = ib + t; j < K; j += 256) {
-      double T[kPanel];
-#pragma unroll
-      for (int r = 0; r < kPanel; ++r) T[r] = (r < nb && ib + r == j) ? 1.0 : 0.0;
-#pragma unroll 8
-      for (int s2 = ib + nb; s2 <= j; ++s2) {
-        const double x = Gb[(int64_t)s2 * K + j];
-#pragma unroll
-        for (int r = 0; r < kPanel; ++r)
-          if (r < nb) T[r] -= Pn[r][s2] * x;
-      }
-#pragma unroll
-      for (int r = kPanel - 1; r >= 0; --r) {
-        if (r < nb) {
-          double v = T[r];
-#pragma unroll
-          for (int q = r + 1; q < kPanel; ++q)
-            if (q < nb) v -= Pn[r][ib + q] * T[q];
-          T[r] = v / Pn[r][ib + r];
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < kPanel; ++r) {
-        if (r < nb && ib + r <= j) {
-          Gb[(int64_t)(ib + r) * K + j] = T[r];
-          Pc[(int64_t)j * (j + 1) / 2 + ib + r] = T[r];
-        }
-      }
-    }
-    __syncthreads();
-  }
-}
-
 // Patch blocks from the assembled subdomain blocks: column c of patch b is feature c mod K of its
 // member c / K (members[moff[b]..], lexicographic in the per-axis indices), on the patch's box,
 // zero where the point lies outside the member's box and in the row padding.  One workgroup per
@@ -507,30 +245,6 @@ hipError_t launch_bt_gram_diag(const DevBlock* blocks, const GramTask* tasks, in
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_bt_gram_diag, dim3((unsigned)n_tasks), dim3(256), lds, s, blocks, tasks, A,
                      goff, G);
-  return hipGetLastError();
-}
-
-hipError_t launch_bt_bj_factor(const DevBlock* blocks, int blk0, int64_t n_blocks,
-                               const double* G, const int64_t* goff, const int64_t* foff, int kmax,
-                               double shift, double* rc, int32_t* nfail, hipStream_t s) {
-  if (n_blocks == 0) return hipSuccess;
-  if (kmax < 1 || kmax > kBatchMaxK) return hipErrorInvalidValue;
-  const size_t lds = (size_t)kmax * (kmax + 1) * sizeof(double);    // two packed triangles
-  hipError_t e = hipFuncSetAttribute((const void*)k_bt_bj_factor,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_bt_bj_factor, dim3((unsigned)n_blocks), dim3(kFacThreads), lds, s, blocks,
-                     blk0, G, goff, foff, shift, rc, nfail);
-  return hipGetLastError();
-}
-
-hipError_t launch_bt_bj_factor_blocked(const DevBlock* blocks, int blk0, int64_t n_blocks,
-                                       double* G, double* W, const int64_t* goff,
-                                       const int64_t* foff, double shift, double* rc,
-                                       int32_t* nfail, hipStream_t s) {
-  if (n_blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_bt_bj_factor_blocked, dim3((unsigned)n_blocks), dim3(256), 0, s, blocks,
-                     blk0, G, W, goff, foff, shift, rc, nfail);
   return hipGetLastError();
 }
 

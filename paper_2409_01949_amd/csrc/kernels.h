@@ -136,7 +136,7 @@ hipError_t launch_gram(const Geo& g, int prec, const DevBlock* blocks, const Gra
                        int64_t n_multi, const void* A, void* G, void* part, hipStream_t s);
 size_t gram_smem_bytes(int prec, int K);
 
-// ---- block-Jacobi preconditioner (k_precond.hip)
+// ---- block-Jacobi preconditioner (k_precond.hip; the factors: k_factor.hip)
 int bj_wg(const Geo& g);
 hipError_t launch_bj_factor(const Geo& g, const double* G, const int64_t* diag_off, double shift,
                             double* work, double* rinv, double* rinvT, int32_t* nfail,
@@ -189,16 +189,11 @@ hipError_t launch_bt_recover_plain(int64_t n, const double* y, const double* x0,
 hipError_t launch_bt_gram_diag(const DevBlock* blocks, const GramTask* tasks, int64_t n_tasks,
                                bool two_panels, const double* A, const int64_t* goff, double* G,
                                hipStream_t s);
-// blocks blk0 .. blk0 + n_blocks - 1; kmax: their largest nk (<= kBatchMaxK; sets the dynamic
-// LDS of two packed triangles)
-hipError_t launch_bt_bj_factor(const DevBlock* blocks, int blk0, int64_t n_blocks,
-                               const double* G, const int64_t* goff, const int64_t* foff, int kmax,
+// factors of blocks blk0 .. blk0 + n_blocks - 1 (k_factor.hip); kmax: their largest nk (<=
+// kPatchMaxK).  W: scratch beside G (both nk x nk at goff); G is overwritten
+hipError_t launch_bt_bj_factor(const DevBlock* blocks, int blk0, int64_t n_blocks, int kmax,
+                               double* G, double* W, const int64_t* goff, const int64_t* foff,
                                double shift, double* rc, int32_t* nfail, hipStream_t s);
-// blocks of up to kPatchMaxK columns: W scratch beside G (both nk x nk at goff); G is overwritten
-hipError_t launch_bt_bj_factor_blocked(const DevBlock* blocks, int blk0, int64_t n_blocks,
-                                       double* G, double* W, const int64_t* goff,
-                                       const int64_t* foff, double shift, double* rc,
-                                       int32_t* nfail, hipStream_t s);
 // patch blocks (FP64, their own layout) from the subdomain blocks of the assembled M
 hipError_t launch_bt_expand(const Geo* geos, const DevBlock* pblocks, const Tile* runs,
                             int64_t n_runs, const DevBlock* blocks, const int32_t* members,
