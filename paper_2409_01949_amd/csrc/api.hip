@@ -424,8 +424,9 @@ int64_t footprint(elmfb_problem h) {
   const Geo& g = h->geo;
   int64_t b = 0;
   auto add = [&](int64_t n) { b += (n + 255) / 256 * 256; };
-  add(h->n_store * 8);                                    // FP64 matrix
-  if (h->lo_prec != ELMFB_FP64) add(h->n_store * elem_size(h->lo_prec));   // low-precision copy
+  add(h->n_store * 8 + kStoreSlack);                      // FP64 matrix
+  if (h->lo_prec != ELMFB_FP64)
+    add(h->n_store * elem_size(h->lo_prec) + kStoreSlack);   // low-precision copy
   add(h->n_block_points * 8);                             // tpart
   add((int64_t)h->chunks.size() * g.K * 8);               // part
   add(4 * 2 * kRedBlocks * 8);                            // reductions
@@ -566,8 +567,10 @@ elmfb_status elmfb_define_problem(const elmfb_problem_desc* desc_in, elmfb_probl
                                               hipGetErrorString(e_));      \
     }                                                                       \
   } while (0)
-  ALLOC(h->d_A, h->n_store * 8);
-  if (h->lo_prec != ELMFB_FP64) ALLOC(h->d_A_lo, h->n_store * elem_size(h->lo_prec));
+  // the Gram kernels read runs of points in whole loads, up to 14 bytes past the last point
+  ALLOC(h->d_A, h->n_store * 8 + kStoreSlack);
+  if (h->lo_prec != ELMFB_FP64)
+    ALLOC(h->d_A_lo, h->n_store * elem_size(h->lo_prec) + kStoreSlack);
   ALLOC(h->d_tpart, h->n_block_points * 8);
   ALLOC(h->d_part, (int64_t)h->chunks.size() * g.K * 8);
   ALLOC(h->d_red, 4 * 2 * kRedBlocks * 8);

@@ -11,6 +11,7 @@ namespace elmfb {
 constexpr int kMaxLevels = ELMFB_MAX_LEVELS;
 constexpr int kTile = 256;          // points per assembly / A.v tile (one per thread)
 constexpr int kRowAlign = 8;        // stored rows start on 8-element boundaries (16 B in FP16)
+constexpr int kStoreSlack = 64;     // bytes allocated past a stored matrix
 constexpr int kChunkPts = 2048;     // points per A^T u chunk (8 per thread of 256)
 constexpr int kHistCap = 32768;     // bidiagonalisation steps an LSQR run records
 constexpr int kRedBlocks = 1024;    // upper bound on per-workgroup partial sums of a reduction
@@ -39,21 +40,33 @@ struct DevBlock {
                     // block-Jacobi preconditioner, the columns of all its member subdomains
 };
 
-constexpr int kGramChunk = 4096;  // shared points per Gram chunk
 
 // One overlapping pair (bi <= bj) of subdomain blocks and its shared box of grid points.
 struct GramPair {
   int32_t bi, bj;
   int32_t ix0, nx, iy0, ny;   // shared box
   int64_t g_off;              // element offset of G_ij [K][K] in the Gram storage
-  int32_t c0, nchunks;        // first global chunk, number of chunks
+  int32_t nchunks;            // number of chunks
   int64_t p_off;              // first partial slot (pairs with several chunks)
 };
 
 struct GramChunk {
-  int32_t pair;
-  int32_t s0;                 // first shared point of the chunk (box row-major)
+  int32_t pair;               // -1: an empty entry (launch order padding)
+  int32_t slot;               // its number among the pair's chunks
+  int32_t s0;                 // first load of the chunk (the loads of the pair's runs in turn)
 };
+
+// The shared box of a pair as runs of consecutive points of both blocks: its grid rows, or one
+// run where it spans the full height of both.
+__host__ __device__ inline void gram_runs(const GramPair& p, const DevBlock& bi, const DevBlock& bj,
+                                          int* rows, int* len) {
+  const bool whole = p.ny == bi.ny && p.ny == bj.ny;
+  *rows = whole ? 1 : p.nx;
+  *len = whole ? p.nx * p.ny : p.ny;
+}
+
+// Side of the square of outputs one workgroup computes: K rounded up to 32, at most 128.
+inline int gram_square(int K) { return K > 96 ? 128 : (K + 31) / 32 * 32; }
 
 // ---- batches of independent instances with several right-hand sides
 constexpr int kMaxRhs = 8;

@@ -6,85 +6,40 @@
 // random features of one subdomain are the main source of the condition numbers of M, Sec. 5),
 // with the ragged K of the instances.
 #include "device.h"
+#include "gram_core.h"
 #include "kernels.h"
 
 namespace elmfb {
 
 typedef double d4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kGdStage = 32;   // points per LDS stage
-constexpr int kGdStr = kGdStage + 1;
-
-// One tile of G_b (a GramTask: rows i0.., columns j0.., at most 128 each) in 16 x 16 MFMA tiles,
-// FP64 inputs and accumulation on v_mfma_f64_16x16x4_f64; on the diagonal tile only the tiles
-// I <= J.  One workgroup per task, the block's points staged 32 at a time (feature-major rows
-// i0.. in X and, off the diagonal, rows j0.. in Y: dynamic LDS of one or two panels).
+// One square of G_b (a GramTask: rows i0.., columns j0.., at most 128 each; on the diagonal the
+// tiles I <= J), FP64, over all points of the block (gram_product).  8,192 blocks of K = 64 to 128
+// 1,944 -> 955 us, patches of up to 512 columns (16 instances) 1,741 -> 958 us, against tiles dealt
+// with a search per product and stages of 32 points without prefetch.
 __global__ void __launch_bounds__(256) k_bt_gram_diag(const DevBlock* __restrict__ blocks,
                                                       const GramTask* __restrict__ tasks,
                                                       const double* __restrict__ A,
                                                       const int64_t* __restrict__ goff,
                                                       double* __restrict__ G) {
-  extern __shared__ double gd_lds[];
+  extern __shared__ gr_vec gd_lds[];
   const GramTask T = tasks[blockIdx.x];
   const DevBlock B = blocks[T.blk];
   const int K = B.nk;
-  const bool diag = T.i0 == T.j0;
-  double* X = gd_lds;
-  double* Y = diag ? gd_lds : gd_lds + kBatchMaxK * kGdStr;
-  const int ni = min(kBatchMaxK, K - T.i0), nj = min(kBatchMaxK, K - T.j0);
-  const int nTi = (ni + 15) >> 4, nTj = (nj + 15) >> 4;
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int li = lane & 15, lq = lane >> 4;
-  const double* Ab = A + B.a_off;
-  const int n = B.n;
-  d4_t acc[16];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = d4_t{0, 0, 0, 0};
-  for (int p0 = 0; p0 < n; p0 += kGdStage) {
-    for (int e = threadIdx.x; e < nTi * 16 * kGdStage; e += 256) {
-      const int k = e / kGdStage, c = e - (e / kGdStage) * kGdStage;
-      X[k * kGdStr + c] = (k < ni && p0 + c < n) ? Ab[(int64_t)(T.i0 + k) * B.ld + p0 + c] : 0.0;
-    }
-    if (!diag) {
-      for (int e = threadIdx.x; e < nTj * 16 * kGdStage; e += 256) {
-        const int k = e / kGdStage, c = e - (e / kGdStage) * kGdStage;
-        Y[k * kGdStr + c] = (k < nj && p0 + c < n) ? Ab[(int64_t)(T.j0 + k) * B.ld + p0 + c] : 0.0;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int t = wid + 4 * i;
-      if (t < nTi * nTj) {
-        const int I = t / nTj, J = t - (t / nTj) * nTj;
-        if (!diag || I <= J) {
-          const double* xr = X + (I * 16 + li) * kGdStr;
-          const double* yr = Y + (J * 16 + li) * kGdStr;
-#pragma unroll
-          for (int q = 0; q < kGdStage; q += 4)
-            acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(xr[q + lq], yr[q + lq], acc[i], 0, 0, 0);
-        }
-      }
-    }
-    __syncthreads();
-  }
-  // v_mfma_f64_16x16x4_f64 accumulator: lane holds column li, rows lq + 4 v
-  double* Gb = G + goff[T.blk];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int t = wid + 4 * i;
-    if (t < nTi * nTj) {
-      const int I = t / nTj, J = t - (t / nTj) * nTj;
-      if (!diag || I <= J) {
-        const int col = J * 16 + li;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int row = I * 16 + lq + 4 * v;
-          if (row < ni && col < nj) Gb[(int64_t)(T.i0 + row) * K + T.j0 + col] = acc[i][v];
-        }
-      }
-    }
-  }
+  GramRun R;
+  R.ldx = R.ldy = (int64_t)B.ld * 8;
+  R.x = reinterpret_cast<const char*>(A + B.a_off) + T.i0 * R.ldx;
+  R.y = reinterpret_cast<const char*>(A + B.a_off) + T.j0 * R.ldy;
+  R.stepx = R.stepy = 0;
+  R.nx = min(kBatchMaxK, K - T.i0);
+  R.ny = min(kBatchMaxK, K - T.j0);
+  R.len = B.n;
+  R.v0 = 0;
+  R.v1 = B.n;
+  double* out = G + goff[T.blk] + (int64_t)T.i0 * K + T.j0;
+  auto put = [&](int r, int c, double v) { out[r * K + c] = v; };
+  if (T.i0 == T.j0) gram_product<ELMFB_FP64, 4, GRAM_UPPER>(R, gd_lds, put);
+  else gram_product<ELMFB_FP64, 4, GRAM_SQUARE>(R, gd_lds, put);
 }
 
 // Fold the preconditioner into the matrix: Mhat_b = M_b R_b^{-1}, i.e. in the feature-major
@@ -239,10 +194,12 @@ hipError_t launch_bt_gram_diag(const DevBlock* blocks, const GramTask* tasks, in
                                bool two_panels, const double* A, const int64_t* goff, double* G,
                                hipStream_t s) {
   if (n_tasks == 0) return hipSuccess;
-  const size_t lds = (size_t)(two_panels ? 2 : 1) * kBatchMaxK * kGdStr * sizeof(double);
-  hipError_t e = hipFuncSetAttribute((const void*)k_bt_gram_diag,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
+  const size_t lds = (size_t)(two_panels ? 2 : 1) * kBatchMaxK * kGrStride * sizeof(gr_vec);
+  if (two_panels) {   // 68 KB
+    const hipError_t e = hipFuncSetAttribute((const void*)k_bt_gram_diag,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(k_bt_gram_diag, dim3((unsigned)n_tasks), dim3(256), lds, s, blocks, tasks, A,
                      goff, G);
   return hipGetLastError();

@@ -2,198 +2,85 @@
 // supports share (the block decomposition of Sec. 3, eq. multilevel_domain_decomp, gives
 // M^T M = sum_ij W_i^T M_i^T V_i V_j^T M_j W_j, nonzero only where I_i and I_j intersect).
 //
-// Each overlapping pair (i <= j) has a rectangular shared box; its points are split into chunks
-// of kGramChunk consecutive points (box row-major).  One workgroup per (chunk, group of <= 64
-// output tiles of 16 x 16) stages 32 points of both blocks ([K][32] each, feature-major) in LDS
-// and accumulates X Y^T on the matrix cores:
-//   FP64 blocks: v_mfma_f64_16x16x4_f64 (8 steps per stage),
-//   FP32 blocks: v_mfma_f32_16x16x4_f32 (8 steps),
-//   BF16 blocks: v_mfma_f32_16x16x32_bf16 (1 step), FP32 accumulation,
-//   FP16 blocks: v_mfma_f32_16x16x32_f16 (1 step), FP32 accumulation.
-// A pair with one chunk writes its block directly; a pair with several chunks writes chunk
-// partials that a second kernel sums in chunk order (deterministic, no atomics).
+// Each overlapping pair (i <= j) has a rectangular shared box, whose grid rows are runs of
+// consecutive points of both blocks; its loads are split into chunks.  One workgroup per
+// (chunk, square of 32 WT x 32 WT outputs) runs gram_product on the stored precision: FP64
+// v_mfma_f64_16x16x4_f64, FP32 v_mfma_f32_16x16x4_f32, 16-bit v_mfma_f32_16x16x32 with FP32
+// accumulation.  A diagonal block computes the upper tiles and writes their mirror images (the
+// same products in the same order).  A pair with one chunk writes its block directly; a pair with
+// several chunks writes chunk partials that a second kernel sums in chunk order (deterministic,
+// no atomics).
 #include "device.h"
+#include "gram_core.h"
 #include "kernels.h"
 
 namespace elmfb {
 
-typedef double d4_t __attribute__((ext_vector_type(4)));
-typedef float f4_t __attribute__((ext_vector_type(4)));
-typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
-typedef _Float16 h8_t __attribute__((ext_vector_type(8)));
-
-constexpr int kStage = 32;        // points per LDS stage
-constexpr int kGramPf = 16;       // register-prefetched entries per thread (K <= 128)
-
-template <int PREC> struct GramTypes;
-template <> struct GramTypes<ELMFB_FP64> { typedef double in_t; typedef double acc_t; typedef d4_t v4; };
-template <> struct GramTypes<ELMFB_FP32> { typedef float in_t; typedef float acc_t; typedef f4_t v4; };
-template <> struct GramTypes<ELMFB_BF16> { typedef __bf16 in_t; typedef float acc_t; typedef f4_t v4; };
-template <> struct GramTypes<ELMFB_FP16> { typedef _Float16 in_t; typedef float acc_t; typedef f4_t v4; };
-
-template <int PREC>
-__device__ __forceinline__ typename GramTypes<PREC>::in_t load_in(const void* A, int64_t i);
-template <>
-__device__ __forceinline__ double load_in<ELMFB_FP64>(const void* A, int64_t i) {
-  return static_cast<const double*>(A)[i];
-}
-template <>
-__device__ __forceinline__ float load_in<ELMFB_FP32>(const void* A, int64_t i) {
-  return static_cast<const float*>(A)[i];
-}
-template <>
-__device__ __forceinline__ __bf16 load_in<ELMFB_BF16>(const void* A, int64_t i) {
-  const uint16_t bits = static_cast<const uint16_t*>(A)[i];
-  return __builtin_bit_cast(__bf16, bits);
-}
-template <>
-__device__ __forceinline__ _Float16 load_in<ELMFB_FP16>(const void* A, int64_t i) {
-  return static_cast<const _Float16*>(A)[i];
-}
-
-// TPW output tiles of 16 x 16 per wave (4 TPW per workgroup): 4 for K <= 64, 9 for K <= 96,
-// 16 above, so that the accumulators of small K leave room for the prefetch registers.
-template <int PREC, int TPW>
+// Bound: FP64 by the matrix cores, 16-bit by the caches (a pair reads 2 K S entries for 2 K^2 S
+// flops); the host orders the chunks so that the pairs of one block follow each other on one XCD's
+// L2.  Staged before with one entry per load, every feature row by every group of output tiles,
+// chunks of 4,096 points whatever their number; computations, before -> now:
+//   3-level problem, 5,361 pairs of K = 96: FP64 9.6 -> 8.5 ms (47 TFLOP/s), FP32 5.9 -> 4.6,
+//     FP16 3.3 -> 1.9 ms (213 TFLOP/s); its diagonal blocks 1,522 -> 767, 964 -> 423, 557 -> 208 us
+//   11 blocks of K = 256: 1,957 -> 501, 1,642 -> 264, 1,167 -> 78 us
+//   256 blocks of K = 16: 50 -> 20, 34 -> 14, 31 -> 11 us
+// (16 loads a row and stage instead of 8 take the registers of a wavefront a SIMD: FP64 8.7 -> 14 ms;
+// one contiguous range of chunks per XCD instead of dealt groups leaves the one with the coarse
+// blocks behind: FP16 2.3 -> 3.0 ms.)
+template <int PREC, int WT>
 __global__ void __launch_bounds__(256) k_gram(Geo g, const DevBlock* __restrict__ blocks,
                                               const GramPair* __restrict__ pairs,
-                                              const GramChunk* __restrict__ chunks,
+                                              const GramChunk* __restrict__ chunks, int chunk_vecs,
                                               const void* __restrict__ A,
-                                              typename GramTypes<PREC>::acc_t* __restrict__ G,
-                                              typename GramTypes<PREC>::acc_t* __restrict__ part) {
-  typedef typename GramTypes<PREC>::in_t in_t;
-  typedef typename GramTypes<PREC>::acc_t acc_t;
-  typedef typename GramTypes<PREC>::v4 v4;
-  constexpr bool k16 = PREC == ELMFB_BF16 || PREC == ELMFB_FP16;
-  constexpr int STR = k16 ? (kStage + 8) : (kStage + 1);   // LDS row stride
-  extern __shared__ __align__(16) unsigned char smem[];
+                                              typename GramT<PREC>::out* __restrict__ G,
+                                              typename GramT<PREC>::out* __restrict__ part) {
+  constexpr int ES = GramT<PREC>::es, VE = sizeof(typename GramLoad<PREC, WT>::t) / ES, M = 32 * WT;
+  extern __shared__ gr_vec lds[];              // 2 x M rows
   const int K = g.K;
-  const int Kp = (K + 15) & ~15;
-  in_t* X = reinterpret_cast<in_t*>(smem);
-  in_t* Y = X + (size_t)Kp * STR;
-
+  const int nsq = (K + M - 1) / M;
+  const int i0 = (int)blockIdx.y / nsq * M, j0 = (int)blockIdx.y % nsq * M;
   const GramChunk ck = chunks[blockIdx.x];
+  if (ck.pair < 0) return;
   const GramPair pr = pairs[ck.pair];
-  const DevBlock Bi = blocks[pr.bi], Bj = blocks[pr.bj];
-  const int nshared = pr.nx * pr.ny;
-  const int s_end = min(ck.s0 + kGramChunk, nshared);
-  const int nT = Kp / 16;
-  const int ntiles = nT * nT;
-  const int t_base = blockIdx.y * 4 * TPW;
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int li = lane & 15, lq = lane >> 4;
-  // a diagonal block G_jj multiplies the staged rows by themselves: stage them once
   const bool diag = pr.bi == pr.bj;
-  const in_t* Yop = diag ? X : Y;
-
-  v4 acc[TPW];
-#pragma unroll
-  for (int i = 0; i < TPW; ++i) acc[i] = v4{0, 0, 0, 0};
-
-  // every thread stages one point slot (s_l) of the stage for features k_l, k_l + 8, ...; the
-  // next stage's entries are loaded into registers while the matrix cores work on this one
-  const int s_l = threadIdx.x & (kStage - 1), k_l = threadIdx.x >> 5;
-  constexpr int kRows = 256 / kStage;            // feature rows per pass (8)
-  in_t rx[kGramPf], ry[kGramPf];
-  const int npf = Kp / kRows;                    // passes (<= kGramPf when prefetching)
-  auto point_idx = [&](int s0, int& pi, int& pj) {
-    const int s = s0 + s_l;
-    pi = pj = -1;
-    if (s < s_end) {
-      const int sx = s / pr.ny, sy = s - sx * pr.ny;
-      const int ix = pr.ix0 + sx, iy = pr.iy0 + sy;
-      pi = (ix - Bi.ix0) * Bi.ny + (iy - Bi.iy0);
-      pj = (ix - Bj.ix0) * Bj.ny + (iy - Bj.iy0);
-    }
-  };
-  auto fetch = [&](int s0) {
-    int pi, pj;
-    point_idx(s0, pi, pj);
-#pragma unroll
-    for (int m = 0; m < kGramPf; ++m) {
-      const int k = k_l + kRows * m;
-      in_t xv = in_t(0.0f), yv = in_t(0.0f);
-      if (m < npf && k < K && pi >= 0) {
-        xv = load_in<PREC>(A, Bi.a_off + (int64_t)k * Bi.ld + pi);
-        if (!diag) yv = load_in<PREC>(A, Bj.a_off + (int64_t)k * Bj.ld + pj);
-      }
-      rx[m] = xv;
-      ry[m] = yv;
-    }
-  };
-  const bool pf = npf <= kGramPf;
-  if (pf) fetch(ck.s0);
-  for (int s0 = ck.s0; s0 < s_end; s0 += kStage) {
-    __syncthreads();   // the previous stage's products are done with X and Y
-    if (pf) {
-#pragma unroll
-      for (int m = 0; m < kGramPf; ++m) {
-        if (m < npf) {
-          const int k = k_l + kRows * m;
-          X[k * STR + s_l] = rx[m];
-          if (!diag) Y[k * STR + s_l] = ry[m];
-        }
-      }
-    } else {
-      int pi, pj;
-      point_idx(s0, pi, pj);
-      for (int k = k_l; k < Kp; k += kRows) {
-        in_t xv = in_t(0.0f), yv = in_t(0.0f);
-        if (k < K && pi >= 0) {
-          xv = load_in<PREC>(A, Bi.a_off + (int64_t)k * Bi.ld + pi);
-          if (!diag) yv = load_in<PREC>(A, Bj.a_off + (int64_t)k * Bj.ld + pj);
-        }
-        X[k * STR + s_l] = xv;
-        if (!diag) Y[k * STR + s_l] = yv;
-      }
-    }
-    __syncthreads();
-    if (pf && s0 + kStage < s_end) fetch(s0 + kStage);
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      const int t = t_base + wid + 4 * i;
-      if (t < ntiles) {
-        const int I = t / nT, J = t - (t / nT) * nT;
-        const in_t* xr = X + (I * 16 + li) * STR;
-        const in_t* yr = Yop + (J * 16 + li) * STR;
-        if constexpr (PREC == ELMFB_BF16) {
-          bf8_t a, b;
-#pragma unroll
-          for (int q = 0; q < 8; ++q) { a[q] = xr[8 * lq + q]; b[q] = yr[8 * lq + q]; }
-          acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[i], 0, 0, 0);
-        } else if constexpr (PREC == ELMFB_FP16) {
-          h8_t a, b;
-#pragma unroll
-          for (int q = 0; q < 8; ++q) { a[q] = xr[8 * lq + q]; b[q] = yr[8 * lq + q]; }
-          acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, acc[i], 0, 0, 0);
-        } else if constexpr (PREC == ELMFB_FP32) {
-#pragma unroll
-          for (int q = 0; q < kStage; q += 4)
-            acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(xr[q + lq], yr[q + lq], acc[i], 0, 0, 0);
-        } else {
-#pragma unroll
-          for (int q = 0; q < kStage; q += 4)
-            acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(xr[q + lq], yr[q + lq], acc[i], 0, 0, 0);
-        }
-      }
-    }
-    __syncthreads();
-  }
-  // accumulator layout of a 16 x 16 tile: lane holds column li; rows 4*lq + v for the FP32
-  // accumulating forms, rows lq + 4*v for v_mfma_f64_16x16x4_f64
-  acc_t* out = (pr.nchunks == 1) ? G + pr.g_off
-                                 : part + (int64_t)(blockIdx.x - pr.c0 + pr.p_off) * K * K;
-#pragma unroll
-  for (int i = 0; i < TPW; ++i) {
-    const int t = t_base + wid + 4 * i;
-    if (t < ntiles) {
-      const int I = t / nT, J = t - (t / nT) * nT;
-      const int col = J * 16 + li;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int row = (PREC == ELMFB_FP64) ? I * 16 + lq + 4 * v : I * 16 + 4 * lq + v;
-        if (row < K && col < K) out[(int64_t)row * K + col] = acc[i][v];
-      }
-    }
+  if (diag && i0 > j0) return;                 // the mirror image of square (j0, i0)
+  const DevBlock Bi = blocks[pr.bi], Bj = blocks[pr.bj];
+  GramRun R;
+  const int64_t pi = (int64_t)(pr.ix0 - Bi.ix0) * Bi.ny + (pr.iy0 - Bi.iy0);
+  const int64_t pj = (int64_t)(pr.ix0 - Bj.ix0) * Bj.ny + (pr.iy0 - Bj.iy0);
+  R.ldx = (int64_t)Bi.ld * ES;
+  R.ldy = (int64_t)Bj.ld * ES;
+  R.x = static_cast<const char*>(A) + (Bi.a_off + pi) * ES + i0 * R.ldx;
+  R.y = static_cast<const char*>(A) + (Bj.a_off + pj) * ES + j0 * R.ldy;
+  R.stepx = (int64_t)Bi.ny * ES;
+  R.stepy = (int64_t)Bj.ny * ES;
+  R.nx = min(M, K - i0);
+  R.ny = min(M, K - j0);
+  int rows;
+  gram_runs(pr, Bi, Bj, &rows, &R.len);
+  R.v0 = ck.s0;
+  R.v1 = min(ck.s0 + chunk_vecs, rows * ((R.len + VE - 1) / VE));
+  typename GramT<PREC>::out* out =
+      (pr.nchunks == 1) ? G + pr.g_off : part + (pr.p_off + ck.slot) * K * K;
+  if (!diag) {
+    auto put = [&](int r, int c, typename GramT<PREC>::out v) { out[(i0 + r) * K + j0 + c] = v; };
+    // An odd number of tiles a side (K = 48): the squares of four wavefronts hold 4, 2, 2 and 1 of
+    // 9 tiles, dealt they hold 3, 2, 2, 2.  16-bit entries deal up to 64 columns only: beyond, they
+    // need the squares' reuse of fragments (a product takes as long as its two LDS reads).
+    if ((PREC == ELMFB_FP64 || PREC == ELMFB_FP32 || WT <= 2) && ((K + 15) / 16) % 2 != 0)
+      gram_product<PREC, WT, GRAM_DEALT>(R, lds, put);
+    else
+      gram_product<PREC, WT, GRAM_SQUARE>(R, lds, put);
+  } else if (i0 == j0) {
+    gram_product<PREC, WT, GRAM_UPPER>(R, lds, [&](int r, int c, typename GramT<PREC>::out v) {
+      out[(i0 + r) * K + i0 + c] = v;
+      if ((r >> 4) != (c >> 4)) out[(i0 + c) * K + i0 + r] = v;
+    });
+  } else {
+    gram_product<PREC, WT, GRAM_SQUARE>(R, lds, [&](int r, int c, typename GramT<PREC>::out v) {
+      out[(i0 + r) * K + j0 + c] = v;
+      out[(j0 + c) * K + i0 + r] = v;
+    });
   }
 }
 
@@ -212,57 +99,57 @@ __global__ void __launch_bounds__(256) k_gram_reduce(Geo g, const GramPair* __re
   }
 }
 
-static size_t gram_smem(int prec, int K) {
-  const int Kp = (K + 15) & ~15;
-  const size_t es = prec == ELMFB_FP64 ? 8 : (prec == ELMFB_FP32 ? 4 : 2);
-  const int str = (prec == ELMFB_BF16 || prec == ELMFB_FP16) ? kStage + 8 : kStage + 1;
-  return 2 * (size_t)Kp * str * es + 2 * kStage * sizeof(int) + 16;
+template <int PREC>
+static int load_points(int K) {
+  const size_t b = gram_square(K) == 96 ? sizeof(typename GramLoad<PREC, 3>::t)
+                                        : sizeof(typename GramLoad<PREC, 1>::t);
+  return (int)b / GramT<PREC>::es;
 }
 
-template <int PREC, int TPW>
-static hipError_t gram_launch(const Geo& g, const DevBlock* blocks, const GramPair* pairs,
-                              const GramChunk* chunks, int64_t n_chunks, const void* A, void* G,
-                              void* part, size_t sm, hipStream_t s) {
-  typedef typename GramTypes<PREC>::acc_t acc_t;
-  const int Kp = (g.K + 15) & ~15;
-  const int nT = Kp / 16;
-  const int groups = (nT * nT + 4 * TPW - 1) / (4 * TPW);
-  if (sm > 64 * 1024) {
-    const hipError_t ea = hipFuncSetAttribute((const void*)k_gram<PREC, TPW>,
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
-    if (ea != hipSuccess) return ea;
-  }
-  hipLaunchKernelGGL((k_gram<PREC, TPW>), dim3((unsigned)n_chunks, (unsigned)groups), dim3(256),
-                     sm, s, g, blocks, pairs, chunks, A, (acc_t*)G, (acc_t*)part);
-  return hipGetLastError();
+int gram_load_points(int prec, int K) {
+  return prec == ELMFB_FP64   ? load_points<ELMFB_FP64>(K)
+         : prec == ELMFB_FP32 ? load_points<ELMFB_FP32>(K)
+         : prec == ELMFB_BF16 ? load_points<ELMFB_BF16>(K)
+                              : load_points<ELMFB_FP16>(K);
 }
 
 template <int PREC>
-static hipError_t gram_launch_k(const Geo& g, const DevBlock* blocks, const GramPair* pairs,
-                                const GramChunk* chunks, int64_t n_chunks, const void* A, void* G,
-                                void* part, size_t sm, hipStream_t s) {
-  if (g.K <= 64) return gram_launch<PREC, 4>(g, blocks, pairs, chunks, n_chunks, A, G, part, sm, s);
-  if (g.K <= 96) return gram_launch<PREC, 9>(g, blocks, pairs, chunks, n_chunks, A, G, part, sm, s);
-  return gram_launch<PREC, 16>(g, blocks, pairs, chunks, n_chunks, A, G, part, sm, s);
+static hipError_t gram_launch(const Geo& g, const DevBlock* blocks, const GramPair* pairs,
+                              const GramChunk* chunks, int64_t n_chunks, int chunk_vecs,
+                              const void* A, void* G, void* part, hipStream_t s) {
+  typedef typename GramT<PREC>::out out_t;
+  const int wt = gram_square(g.K) / 32, nsq = (g.K + 32 * wt - 1) / (32 * wt);
+  const dim3 grid((unsigned)n_chunks, (unsigned)(nsq * nsq));
+  const size_t sm = (size_t)2 * 32 * wt * kGrStride * sizeof(gr_vec);
+  if (wt == 4) {   // 68 KB
+    const hipError_t e = hipFuncSetAttribute((const void*)k_gram<PREC, 4>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
+    if (e != hipSuccess) return e;
+  }
+#define GRAM(W)                                                                                  \
+  hipLaunchKernelGGL((k_gram<PREC, W>), grid, dim3(256), sm, s, g, blocks, pairs, chunks,        \
+                     chunk_vecs, A, (out_t*)G, (out_t*)part)
+  if (wt == 1) GRAM(1); else if (wt == 2) GRAM(2); else if (wt == 3) GRAM(3); else GRAM(4);
+#undef GRAM
+  return hipGetLastError();
 }
 
 hipError_t launch_gram(const Geo& g, int prec, const DevBlock* blocks, const GramPair* pairs,
-                       const GramChunk* chunks, int64_t n_chunks, const int32_t* multi,
-                       int64_t n_multi, const void* A, void* G, void* part, hipStream_t s) {
+                       const GramChunk* chunks, int64_t n_chunks, int chunk_vecs,
+                       const int32_t* multi, int64_t n_multi, const void* A, void* G, void* part,
+                       hipStream_t s) {
   if (n_chunks == 0) return hipSuccess;
-  const size_t sm = gram_smem(prec, g.K);
-  if (sm > 160 * 1024) return hipErrorInvalidValue;
   hipError_t e;
   if (prec == ELMFB_FP64)
-    e = gram_launch_k<ELMFB_FP64>(g, blocks, pairs, chunks, n_chunks, A, G, part, sm, s);
+    e = gram_launch<ELMFB_FP64>(g, blocks, pairs, chunks, n_chunks, chunk_vecs, A, G, part, s);
   else if (prec == ELMFB_FP32)
-    e = gram_launch_k<ELMFB_FP32>(g, blocks, pairs, chunks, n_chunks, A, G, part, sm, s);
+    e = gram_launch<ELMFB_FP32>(g, blocks, pairs, chunks, n_chunks, chunk_vecs, A, G, part, s);
   else if (prec == ELMFB_BF16)
-    e = gram_launch_k<ELMFB_BF16>(g, blocks, pairs, chunks, n_chunks, A, G, part, sm, s);
+    e = gram_launch<ELMFB_BF16>(g, blocks, pairs, chunks, n_chunks, chunk_vecs, A, G, part, s);
   else
-    e = gram_launch_k<ELMFB_FP16>(g, blocks, pairs, chunks, n_chunks, A, G, part, sm, s);
+    e = gram_launch<ELMFB_FP16>(g, blocks, pairs, chunks, n_chunks, chunk_vecs, A, G, part, s);
   if (e != hipSuccess || n_multi == 0) return e;
-  const dim3 rgrid((unsigned)n_multi, (unsigned)((g.K * g.K + 255) / 256 < 16 ? (g.K * g.K + 255) / 256 : 16));
+  const dim3 rgrid((unsigned)n_multi, (unsigned)((g.K * g.K + 255) / 256 < 64 ? (g.K * g.K + 255) / 256 : 64));
   if (prec == ELMFB_FP64)
     hipLaunchKernelGGL(k_gram_reduce<double>, rgrid, dim3(256), 0, s, g, pairs, multi,
                        (const double*)part, (double*)G);
@@ -271,8 +158,6 @@ hipError_t launch_gram(const Geo& g, int prec, const DevBlock* blocks, const Gra
                        (const float*)part, (float*)G);
   return hipGetLastError();
 }
-
-size_t gram_smem_bytes(int prec, int K) { return gram_smem(prec, K); }
 
 // ---- y = G p from the stored upper Gram blocks (the normal-equation operator of CG on G)
 //

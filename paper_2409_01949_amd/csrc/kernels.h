@@ -131,10 +131,12 @@ hipError_t launch_gcg_beta(SolveState* st, const double* red_r, int nr, const do
                            int nz, hipStream_t s);
 hipError_t launch_gcg_pupdate(const Geo& g, double* p, const double* z, const SolveState* st,
                               int init, hipStream_t s);
+// points of one load of the Gram kernel (a chunk starts on a multiple of them within a run)
+int gram_load_points(int prec, int K);
 hipError_t launch_gram(const Geo& g, int prec, const DevBlock* blocks, const GramPair* pairs,
-                       const GramChunk* chunks, int64_t n_chunks, const int32_t* multi,
-                       int64_t n_multi, const void* A, void* G, void* part, hipStream_t s);
-size_t gram_smem_bytes(int prec, int K);
+                       const GramChunk* chunks, int64_t n_chunks, int chunk_vecs,
+                       const int32_t* multi, int64_t n_multi, const void* A, void* G, void* part,
+                       hipStream_t s);
 
 // ---- block-Jacobi preconditioner (k_precond.hip; the factors: k_factor.hip)
 int bj_wg(const Geo& g);

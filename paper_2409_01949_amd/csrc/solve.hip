@@ -371,20 +371,53 @@ elmfb_status run_gram(elmfb_problem h, int prec, std::vector<GramPair>& pairs, v
   const int64_t KK = (int64_t)g.K * g.K;
   std::vector<GramChunk> chunks;
   std::vector<int32_t> multi;
+  const int ve = gram_load_points(prec, g.K);   // points of a load, the unit of chunks
+  auto loads = [&](const GramPair& pr) {
+    int rows, len;
+    gram_runs(pr, h->blocks[pr.bi], h->blocks[pr.bj], &rows, &len);
+    return (int64_t)rows * ((len + ve - 1) / ve);
+  };
+  // loads per chunk: about 8 workgroups a CU over the whole computation, from 512 points (a
+  // workgroup's fixed cost) to 8,192 (longer chunks only unbalance the last wave)
+  const int side = gram_square(g.K), squares = (g.K + side - 1) / side;
+  int64_t total = 0;
+  for (const GramPair& pr : pairs) total += loads(pr) * squares * squares;
+  const int64_t cv64 = std::min<int64_t>(8192 / ve, std::max<int64_t>(512 / ve, total / 2048));
+  const int cv = (int)((cv64 + 31) / 32 * 32);
   int64_t p_off = 0;
   for (size_t p = 0; p < pairs.size(); ++p) {
     GramPair& pr = pairs[p];
-    const int64_t ns = (int64_t)pr.nx * pr.ny;
+    const int64_t nv = loads(pr);
     pr.g_off = (int64_t)p * KK;
-    pr.c0 = (int32_t)chunks.size();
-    pr.nchunks = (int32_t)((ns + kGramChunk - 1) / kGramChunk);
+    pr.nchunks = (int32_t)((nv + cv - 1) / cv);
     pr.p_off = 0;
     if (pr.nchunks > 1) {
       pr.p_off = p_off;
       p_off += pr.nchunks;
       multi.push_back((int32_t)p);
     }
-    for (int64_t s0 = 0; s0 < ns; s0 += kGramChunk) chunks.push_back(GramChunk{(int32_t)p, (int32_t)s0});
+    for (int64_t s0 = 0; s0 < nv; s0 += cv)
+      chunks.push_back(GramChunk{(int32_t)p, (int32_t)(s0 / cv), (int32_t)s0});
+  }
+  // Workgroups go to the 8 XCDs in turn: deal the chunks so that the pairs of one block i follow
+  // each other on one XCD, whose L2 then holds that block, in groups small enough to balance.
+  {
+    constexpr int kXcd = 8, kGroup = 16;
+    std::vector<GramChunk> on[kXcd];
+    int64_t load[kXcd] = {0};
+    for (size_t c = 0; c < chunks.size();) {
+      const int x = (int)(std::min_element(load, load + kXcd) - load);
+      const int32_t bi = pairs[chunks[c].pair].bi;
+      for (int n = 0; c < chunks.size() && n < kGroup && pairs[chunks[c].pair].bi == bi; ++n, ++c) {
+        on[x].push_back(chunks[c]);
+        load[x] += std::min<int64_t>(cv, loads(pairs[chunks[c].pair]) - chunks[c].s0);
+      }
+    }
+    size_t longest = 0;
+    for (const auto& v : on) longest = std::max(longest, v.size());
+    chunks.clear();
+    for (size_t i = 0; i < longest; ++i)
+      for (const auto& v : on) chunks.push_back(i < v.size() ? v[i] : GramChunk{-1, 0, 0});
   }
   const int64_t acc_es = prec == ELMFB_FP64 ? 8 : 4;
   auto grow = [&](void** buf, int64_t* cap, int64_t need) -> hipError_t {
@@ -410,8 +443,9 @@ elmfb_status run_gram(elmfb_problem h, int prec, std::vector<GramPair>& pairs, v
                                   hipMemcpyHostToDevice, s));
   const void* A = prec == ELMFB_FP64 ? (const void*)h->d_A : h->d_A_lo;
   HIP_OR_FAIL(h, launch_gram(g, prec, h->d_blocks, h->d_gpairs, h->d_gchunks,
-                             (int64_t)chunks.size(), h->d_gmulti, (int64_t)multi.size(), A, G,
+                             (int64_t)chunks.size(), cv, h->d_gmulti, (int64_t)multi.size(), A, G,
                              h->d_gpart, s));
+  h->gram_chunk_vecs = cv;
   h->gram_nchunks = (int64_t)chunks.size();
   h->gram_nmulti = (int64_t)multi.size();
   // the host tables above must outlive the asynchronous copies
@@ -564,7 +598,7 @@ elmfb_status elmfb_time_gram(elmfb_problem h, int32_t prec, int32_t which, int32
   hipError_t e = hipEventRecord(e0, s);
   for (int i = 0; i < reps && e == hipSuccess; ++i)
     e = launch_gram(g, prec, h->d_blocks, h->d_gpairs, h->d_gchunks, h->gram_nchunks,
-                    h->d_gmulti, h->gram_nmulti, A, h->d_G, h->d_gpart, s);
+                    h->gram_chunk_vecs, h->d_gmulti, h->gram_nmulti, A, h->d_G, h->d_gpart, s);
   if (e == hipSuccess) e = hipEventRecord(e1, s);
   if (e == hipSuccess) e = hipEventSynchronize(e1);
   float t = 0.f;
