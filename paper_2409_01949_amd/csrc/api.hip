@@ -767,10 +767,8 @@ elmfb_status elmfb_matvec(elmfb_problem h, const double* v_dev, double* y_dev, v
   HIP_OR_FAIL(h, launch_mv_blocks(g, ELMFB_FP64, h->d_blocks, h->d_tiles, (int64_t)h->tiles.size(),
                                   h->d_A, v_dev, nullptr, h->d_tpart, nullptr, s));
   HIP_OR_FAIL(h, launch_gather_rows(g, h->d_blocks, h->d_cov, h->d_tpart, ROW_STORE, y_dev,
-                                    nullptr, nullptr, h->d_red, rows_wg(g), s));
-  if (g.n_bc > 0)
-    HIP_OR_FAIL(h, launch_bc_rows(g, h->d_bc, v_dev, nullptr, ROW_STORE, y_dev, nullptr, nullptr,
-                                  h->d_red + rows_wg(g), s));
+                                    nullptr, nullptr, h->d_red, rows_wg(g), h->d_bc, v_dev,
+                                    nullptr, s));
   return ELMFB_OK;
 }
 

@@ -4,7 +4,7 @@
 //     condition (the damped oscillator's initial conditions, Sec. 4.2);
 //   - 2D Dirichlet rows at points: row b is w (1/L) omega_j phi_q C at x_b (the boundary term of
 //     the Helmholtz loss, Sec. 4.4, with w = sqrt(lambda_bc / N_B)).
-// Their part of M^T u is added by k_rmv_finish.
+// Their products with v and u are formed in k_gather_rows and k_rmv_finish.
 #include "device.h"
 #include "kernels.h"
 
@@ -121,53 +121,6 @@ __global__ void __launch_bounds__(256) k_bc_assemble_pts(Geo g, const DevBlock* 
   if (threadIdx.x == 0) h[g.n_rows + b] = g.bc_w * g.bcpts[2 * (int64_t)g.n_bc + b];
 }
 
-// y_b = sum_q Bm[b][q] v_q (v scaled by *vscale when given) for the soft-constraint rows, one
-// wavefront per row and 4 rows per workgroup, then the row mode at row n_rows + b as
-// k_gather_rows applies it; each workgroup writes one partial squared norm to red[blockIdx.x]
-// (its rows' in order).  Fixed-order sums: deterministic.
-__global__ void __launch_bounds__(256) k_bc_rows(Geo g, const double* __restrict__ Bm,
-                                                 const double* __restrict__ v,
-                                                 const double* __restrict__ vscale, int mode,
-                                                 double* __restrict__ out,
-                                                 const double* __restrict__ bvec,
-                                                 const SolveState* __restrict__ st,
-                                                 double* __restrict__ red) {
-  __shared__ double sh[4];
-  if (st && st->done) return;
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int b = blockIdx.x * 4 + wid;
-  const double sc = vscale ? *vscale : 1.0;
-  double acc = 0.0;
-  if (b < g.n_bc) {
-    const double* row = Bm + (int64_t)b * g.n_phi;
-    double d = 0.0;
-    for (int64_t q = lane; q < g.n_phi; q += 64) d += row[q] * v[q];
-    const double y = wave_sum(d) * sc;
-    if (lane == 0) {
-      const int64_t r = g.n_rows + b;
-      if (mode == ROW_STORE) {
-        out[r] = y;
-      } else if (mode == ROW_LSQR_U) {
-        const double u = y - st->alpha * st->su * out[r];
-        out[r] = u;
-        acc = u * u;
-      } else if (mode == ROW_RESID) {
-        const double u = bvec[r] - y;
-        out[r] = u;
-        acc = u * u;
-      } else {
-        out[r] = y;
-        acc = y * y;
-      }
-    }
-  }
-  if (lane == 0) sh[wid] = acc;
-  __syncthreads();
-  if (mode != ROW_STORE && threadIdx.x == 0) red[blockIdx.x] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
-}
-
-int bc_row_wgs(const Geo& g) { return (g.n_bc + 3) / 4; }
-
 hipError_t launch_bc_assemble(const Geo& g, const BcSpec& bc, const DevBlock* blocks,
                               const double* W, const double* b, double* Bm, double* h,
                               hipStream_t s) {
@@ -182,15 +135,6 @@ hipError_t launch_bc_assemble_pts(const Geo& g, const DevBlock* blocks, const do
   if (g.n_bc == 0) return hipSuccess;
   hipLaunchKernelGGL(k_bc_assemble_pts, dim3((unsigned)g.n_bc), dim3(256), 0, s, g, blocks, W, b,
                      Bm, h);
-  return hipGetLastError();
-}
-
-hipError_t launch_bc_rows(const Geo& g, const double* Bm, const double* v, const double* vscale,
-                          int mode, double* out, const double* bvec, const SolveState* st,
-                          double* red, hipStream_t s) {
-  if (g.n_bc == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_bc_rows, dim3((unsigned)bc_row_wgs(g)), dim3(256), 0, s, g, Bm, v, vscale,
-                     mode, out, bvec, st, red);
   return hipGetLastError();
 }
 

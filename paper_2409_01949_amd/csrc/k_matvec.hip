@@ -82,20 +82,87 @@ __global__ void __launch_bounds__(256) k_mv_blocks(Geo g, const DevBlock* __rest
       tpart[B.p_off + p + q] = ((acc[0][q] + acc[1][q]) + (acc[2][q] + acc[3][q])) * sc;
 }
 
+// y_b = sum_q bc[b][q] v_q (v scaled by *vscale when given) for the soft-constraint rows, one
+// wavefront per row and 4 rows per workgroup, then the row mode at row n_rows + b as
+// k_gather_rows applies it; workgroup `wg` writes one partial squared norm to *red (its rows' in
+// order).  A wavefront keeps 8 of its n_phi / 64 loads in flight (one at a time, the chain of
+// loads was the pass: 320 rows of 3,072 columns 12.7 us).
+__device__ __forceinline__ void bc_rows(const Geo& g, int wg, const double* __restrict__ bc,
+                                        const double* __restrict__ v,
+                                        const double* __restrict__ vscale, int mode,
+                                        double* __restrict__ out, const double* __restrict__ bvec,
+                                        const SolveState* __restrict__ st,
+                                        double* __restrict__ red, double* sh) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int b = wg * 4 + wid;
+  const double sc = vscale ? *vscale : 1.0;
+  double acc = 0.0;
+  if (b < g.n_bc) {
+    const double* row = bc + (int64_t)b * g.n_phi;
+    double d = 0.0;
+    int64_t q = lane;
+    for (; q + 64 * 7 < g.n_phi; q += 64 * 8) {
+      double a[8], x[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        a[i] = row[q + 64 * i];
+        x[i] = v[q + 64 * i];
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) d += a[i] * x[i];
+    }
+    for (; q < g.n_phi; q += 64) d += row[q] * v[q];
+    const double y = wave_sum(d) * sc;
+    if (lane == 0) {
+      const int64_t r = g.n_rows + b;
+      if (mode == ROW_STORE) {
+        out[r] = y;
+      } else if (mode == ROW_LSQR_U) {
+        const double u = y - st->alpha * st->su * out[r];
+        out[r] = u;
+        acc = u * u;
+      } else if (mode == ROW_RESID) {
+        const double u = bvec[r] - y;
+        out[r] = u;
+        acc = u * u;
+      } else {
+        out[r] = y;
+        acc = y * y;
+      }
+    }
+  }
+  if (lane == 0) sh[wid] = acc;
+  __syncthreads();
+  if (mode != ROW_STORE && threadIdx.x == 0) *red = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+}
+
+// With BC the workgroups from n_row_wgs on take the soft-constraint rows (bc, vb, vscale); MAPPED:
+// an L-shaped domain, which discards subdomains (covering blocks through the block map).
+template <bool BC, bool MAPPED>
 __global__ void __launch_bounds__(256) k_gather_rows(Geo g, const DevBlock* __restrict__ blocks,
                                                      const int32_t* __restrict__ cov,
                                                      const double* __restrict__ tpart, int mode,
                                                      double* __restrict__ out,
                                                      const double* __restrict__ bvec,
                                                      const SolveState* __restrict__ st,
-                                                     double* __restrict__ red) {
+                                                     double* __restrict__ red, int n_row_wgs,
+                                                     const double* __restrict__ bc,
+                                                     const double* __restrict__ vb,
+                                                     const double* __restrict__ vscale) {
   __shared__ double sh[4];
   if (st && st->done) return;
+  if constexpr (BC) {
+    if ((int)blockIdx.x >= n_row_wgs) {
+      bc_rows(g, (int)blockIdx.x - n_row_wgs, bc, vb, vscale, mode, out, bvec, st,
+              red + blockIdx.x, sh);
+      return;
+    }
+  }
   double coef_u = 0.0;
   if (mode == ROW_LSQR_U) coef_u = st->alpha * st->su;
   double acc = 0.0;
   for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < g.n_rows;
-       r += (int64_t)gridDim.x * blockDim.x) {
+       r += (int64_t)n_row_wgs * blockDim.x) {
     const int ix = (int)(r / g.ny), iy = (int)(r - (int64_t)ix * g.ny);
     double y = 0.0;
     for (int l = 0; l < g.n_levels; ++l) {
@@ -103,27 +170,33 @@ __global__ void __launch_bounds__(256) k_gather_rows(Geo g, const DevBlock* __re
       const int jy0 = cov[g.cov_off[l][1] + 2 * iy], jy1 = cov[g.cov_off[l][1] + 2 * iy + 1];
       const int Jy = g.J[l][1];
       const int ncx = jx1 - jx0 + 1, ncy = jy1 - jy0 + 1;
-      if (g.domain == ELMFB_DOMAIN_L) {
-        // an L-shaped domain discards subdomains: covering blocks through the block map
-        for (int jx = jx0; jx <= jx1; ++jx)
-          for (int jy = jy0; jy <= jy1; ++jy) {
-            const int bi = g.bmap[g.bmap_off[l] + jx * Jy + jy];
-            if (bi < 0) continue;
-            const DevBlock& B = blocks[bi];
-            y += tpart[B.p_off + (ix - B.ix0) * B.ny + (iy - B.iy0)];
-          }
-      } else if (ncx <= 3 && ncy <= 3) {
+      if (ncx <= 3 && ncy <= 3) {
         // up to 3 x 3 covering blocks (width ratio < 3): every load issued before the sums,
-        // which keep the order jx-major, jy-minor; absent slots read the first block and add 0
+        // which keep the order jx-major, jy-minor; absent slots read the first block (a
+        // discarded one: block 0's first point) and add 0
+        int at[9];
+        if constexpr (MAPPED) {
+#pragma unroll
+          for (int q = 0; q < 9; ++q)
+            at[q] = g.bmap[g.bmap_off[l] + (jx0 + (q / 3 < ncx ? q / 3 : 0)) * Jy + jy0 +
+                           (q % 3 < ncy ? q % 3 : 0)];
+        }
         double tv[9];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
-            const bool ok = a < ncx && c < ncy;
-            const DevBlock& B = blocks[g.bbase[l] + (jx0 + (ok ? a : 0)) * Jy + jy0 + (ok ? c : 0)];
-            const int p = (ix - B.ix0) * B.ny + (iy - B.iy0);
-            const double t = tpart[B.p_off + p];
+            bool ok = a < ncx && c < ncy;
+            double t;
+            if constexpr (MAPPED) {
+              const int bi = at[a * 3 + c];
+              ok = ok && bi >= 0;
+              const DevBlock& B = blocks[ok ? bi : 0];
+              t = tpart[B.p_off + (ok ? (ix - B.ix0) * B.ny + (iy - B.iy0) : 0)];
+            } else {
+              const DevBlock& B = blocks[g.bbase[l] + (jx0 + (ok ? a : 0)) * Jy + jy0 + (ok ? c : 0)];
+              t = tpart[B.p_off + (ix - B.ix0) * B.ny + (iy - B.iy0)];
+            }
             tv[a * 3 + c] = ok ? t : 0.0;
           }
         }
@@ -132,7 +205,9 @@ __global__ void __launch_bounds__(256) k_gather_rows(Geo g, const DevBlock* __re
       } else {
         for (int jx = jx0; jx <= jx1; ++jx) {
           for (int jy = jy0; jy <= jy1; ++jy) {
-            const DevBlock& B = blocks[g.bbase[l] + jx * Jy + jy];
+            const int bi = MAPPED ? g.bmap[g.bmap_off[l] + jx * Jy + jy] : g.bbase[l] + jx * Jy + jy;
+            if (MAPPED && bi < 0) continue;
+            const DevBlock& B = blocks[bi];
             const int p = (ix - B.ix0) * B.ny + (iy - B.iy0);
             y += tpart[B.p_off + p];
           }
@@ -279,7 +354,7 @@ __global__ void __launch_bounds__(256) k_rmv_finish(Geo g, const int32_t* __rest
       for (int q = 0; q < 8; ++q) x += t[q];
     }
     for (; c < ce; ++c) x += part[(int64_t)c * K + k];
-    if (bc) {
+    if (bc) {   // fewer than kSplitBc rows
       const double usc = uscale ? *uscale : 1.0;
       for (int r = 0; r < g.n_bc; ++r) x += bc[(int64_t)r * g.n_phi + q] * (u[g.n_rows + r] * usc);
     }
@@ -303,12 +378,89 @@ __global__ void __launch_bounds__(256) k_rmv_finish(Geo g, const int32_t* __rest
   }
 }
 
+// The same with many soft-constraint rows: a workgroup of 16 wavefronts takes 64 columns, each
+// wavefront every 16th row with up to 8 loads in flight, and the first one adds the 16 sums to
+// the chunk partials.  n_wg workgroups stride over the columns.  One thread per column summing
+// the rows in turn was a chain of n_bc loads: 320 rows of 3,072 columns 41.6 us a
+// pass, now 6.9 (the row pass with them in it 21.4 -> 7.8 us, one launch less).
+constexpr int kBcSlices = 16;
+__global__ void __launch_bounds__(64 * kBcSlices) k_rmv_finish_bc(
+    Geo g, const int32_t* __restrict__ cstart, const double* __restrict__ part, int mode,
+    double* __restrict__ out, const SolveState* __restrict__ st, double* __restrict__ red,
+    const double* __restrict__ bc, const double* __restrict__ u,
+    const double* __restrict__ uscale) {
+  __shared__ double sums[kBcSlices][64];
+  if (st && st->done) return;
+  const int K = g.K;
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const double usc = uscale ? *uscale : 1.0;
+  const double* ub = u + g.n_rows;
+  double coef_v = 0.0;
+  bool keep = false;
+  if (mode == COL_LSQR_V) {
+    coef_v = st->beta * st->sv;
+    keep = !(st->beta > 0.0);
+  }
+  double acc = 0.0;
+  for (int64_t q0 = (int64_t)blockIdx.x * 64; q0 < g.n_phi; q0 += (int64_t)gridDim.x * 64) {
+    const int64_t q = q0 + lane;
+    const bool live = q < g.n_phi;
+    const double* col = bc + (live ? q : q0);
+    double d = 0.0;
+    int r = wid;
+    for (; r + 7 * kBcSlices < g.n_bc; r += 8 * kBcSlices) {
+      double t[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) t[i] = col[(int64_t)(r + i * kBcSlices) * g.n_phi];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) d += t[i] * (ub[r + i * kBcSlices] * usc);
+    }
+    for (; r < g.n_bc; r += kBcSlices) d += col[(int64_t)r * g.n_phi] * (ub[r] * usc);
+    sums[wid][lane] = d;
+    __syncthreads();
+    if (wid == 0 && live) {
+      const int b = (int)(q / K), k = (int)(q - (int64_t)b * K);
+      double x = 0.0;
+      for (int c = cstart[b]; c < cstart[b + 1]; ++c) x += part[(int64_t)c * K + k];
+      double y = 0.0;
+#pragma unroll
+      for (int i = 0; i < kBcSlices; ++i) y += sums[i][lane];
+      x += y;
+      if (mode == COL_STORE) {
+        out[q] = x;
+      } else if (mode == COL_LSQR_V) {
+        double v = out[q];
+        if (!keep) {
+          v = x - coef_v * v;
+          out[q] = v;
+        }
+        acc += v * v;
+      } else {
+        out[q] = x;
+        acc += x * x;
+      }
+    }
+    __syncthreads();
+  }
+  if (mode != COL_STORE && wid == 0) {
+    const double s = wave_sum(acc);
+    if (lane == 0) red[blockIdx.x] = s;
+  }
+}
+
+// Soft-constraint rows from which their sums are split over wavefronts: below, one thread per
+// column adds them in turn (a boundary value problem's one or two rows; every sum as before).
+constexpr int kSplitBc = 16;
+
 int rows_wg(const Geo& g) {
   int64_t nb = (g.n_rows + 255) / 256;
   return (int)(nb < kRedBlocks ? nb : kRedBlocks);
 }
+int bc_row_wgs(const Geo& g) { return (g.n_bc + 3) / 4; }
 int cols_wg(const Geo& g) {
-  int64_t nb = (g.n_phi + 255) / 256;
+  const int per = g.n_bc >= kSplitBc ? 64 : 256;
+  int64_t nb = (g.n_phi + per - 1) / per;
   return (int)(nb < kRedBlocks ? nb : kRedBlocks);
 }
 
@@ -359,10 +511,23 @@ hipError_t launch_mv_blocks(const Geo& g, int prec, const DevBlock* blocks, cons
 
 hipError_t launch_gather_rows(const Geo& g, const DevBlock* blocks, const int32_t* cov,
                               const double* tpart, int mode, double* out, const double* bvec,
-                              const SolveState* st, double* red, int n_wg, hipStream_t s) {
-  hipLaunchKernelGGL(k_gather_rows, dim3(n_wg), dim3(256), 0, s, g, blocks, cov, tpart, mode, out,
-                     bvec, st, red);
+                              const SolveState* st, double* red, int n_wg, const double* bc,
+                              const double* v, const double* vscale, hipStream_t s) {
+  const int n_bc_wg = bc ? bc_row_wgs(g) : 0;
+  const bool mapped = g.domain == ELMFB_DOMAIN_L;
+#define GATHER(BC, M)                                                                            \
+  hipLaunchKernelGGL((k_gather_rows<BC, M>), dim3(n_wg + n_bc_wg), dim3(256), 0, s, g, blocks,   \
+                     cov, tpart, mode, out, bvec, st, red, n_wg, bc, v, vscale)
+  if (n_bc_wg) { if (mapped) GATHER(true, true); else GATHER(true, false); }
+  else { if (mapped) GATHER(false, true); else GATHER(false, false); }
+#undef GATHER
   return hipGetLastError();
+}
+hipError_t launch_gather_rows(const Geo& g, const DevBlock* blocks, const int32_t* cov,
+                              const double* tpart, int mode, double* out, const double* bvec,
+                              const SolveState* st, double* red, int n_wg, hipStream_t s) {
+  return launch_gather_rows(g, blocks, cov, tpart, mode, out, bvec, st, red, n_wg, nullptr, nullptr,
+                            nullptr, s);
 }
 
 template <int PREC>
@@ -397,6 +562,11 @@ hipError_t launch_rmv_finish(const Geo& g, const int32_t* chunk_start, const dou
                              int mode, double* out, const SolveState* st, double* red, int n_wg,
                              const double* bc, const double* u, const double* uscale,
                              hipStream_t s) {
+  if (bc && g.n_bc >= kSplitBc) {
+    hipLaunchKernelGGL(k_rmv_finish_bc, dim3(n_wg), dim3(64 * kBcSlices), 0, s, g, chunk_start, part,
+                       mode, out, st, red, bc, u, uscale);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_rmv_finish, dim3(n_wg), dim3(256), 0, s, g, chunk_start, part, mode, out,
                      st, red, g.n_bc > 0 ? bc : nullptr, u, uscale);
   return hipGetLastError();

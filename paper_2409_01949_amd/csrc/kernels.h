@@ -34,6 +34,13 @@ hipError_t launch_mv_blocks(const Geo& g, int prec, const DevBlock* blocks, cons
 hipError_t launch_gather_rows(const Geo& g, const DevBlock* blocks, const int32_t* cov,
                               const double* tpart, int mode, double* out, const double* bvec,
                               const SolveState* st, double* red, int n_wg, hipStream_t s);
+// the same with the soft-constraint rows bc [n_bc][n_phi] (NULL: none), y_b = bc_b . v (v scaled
+// by *vscale when given): rows n_rows.. of out (and bvec), their norm partials in
+// red[n_wg .. n_wg + bc_row_wgs)
+hipError_t launch_gather_rows(const Geo& g, const DevBlock* blocks, const int32_t* cov,
+                              const double* tpart, int mode, double* out, const double* bvec,
+                              const SolveState* st, double* red, int n_wg, const double* bc,
+                              const double* v, const double* vscale, hipStream_t s);
 // stage 1 of x = A^T u: per chunk partial dot products [n_chunks][K]
 hipError_t launch_rmv_chunks(const Geo& g, int prec, const DevBlock* blocks, const Tile* chunks,
                              int64_t n_chunks, const void* A, const double* u,
@@ -49,19 +56,15 @@ hipError_t launch_rmv_finish(const Geo& g, const int32_t* chunk_start, const dou
                              int mode, double* out, const SolveState* st, double* red, int n_wg,
                              const double* bc, const double* u, const double* uscale,
                              hipStream_t s);
-// Soft-constraint rows (k_bc.hip): assemble them (and their right-hand side entries h[n_rows..]),
-// and their part of y = M v: rows n_rows.. of out in the given RowMode, one partial squared norm
-// to *red (not for ROW_STORE)
+// Soft-constraint rows (k_bc.hip): assemble them (and their right-hand side entries h[n_rows..])
 hipError_t launch_bc_assemble(const Geo& g, const BcSpec& bc, const DevBlock* blocks,
                               const double* W, const double* b, double* Bm, double* h,
                               hipStream_t s);
 hipError_t launch_bc_assemble_pts(const Geo& g, const DevBlock* blocks, const double* W,
                                   const double* b, double* Bm, double* h, hipStream_t s);
-// workgroups of launch_bc_rows, each writing one norm partial
+// workgroups of the soft-constraint rows in the row pass, of its collocation rows, and of the
+// column passes
 int bc_row_wgs(const Geo& g);
-hipError_t launch_bc_rows(const Geo& g, const double* Bm, const double* v, const double* vscale,
-                          int mode, double* out, const double* bvec, const SolveState* st,
-                          double* red, hipStream_t s);
 int rows_wg(const Geo& g);
 int cols_wg(const Geo& g);
 

@@ -70,12 +70,8 @@ hipError_t lsqr_iteration(elmfb_problem h, const KCtx& c, hipStream_t s) {
       return e;
   }
   if ((e = launch_gather_rows(g, h->d_blocks, h->d_cov, h->d_tpart, ROW_LSQR_U, h->d_u, nullptr,
-                              st, red1, rw, s)))
-    return e;
-  // soft-constraint rows: their u entries and one more norm partial
-  if ((e = launch_bc_rows(g, h->d_bc, c.apply ? h->d_vt : h->d_v,
-                          c.apply ? nullptr : state_field(h, offsetof(SolveState, sv)), ROW_LSQR_U,
-                          h->d_u, nullptr, st, red1 + rw, s)))
+                              st, red1, rw, h->d_bc, c.apply ? h->d_vt : h->d_v,
+                              c.apply ? nullptr : state_field(h, offsetof(SolveState, sv)), s)))
     return e;
   if ((e = launch_lsqr_beta(st, red1, rw + bc_parts(g), h->d_hist, s))) return e;
   if ((e = launch_rmv_chunks(g, c.prec, h->d_blocks, h->d_chunks, nc, c.A, h->d_u,
@@ -107,10 +103,7 @@ hipError_t cgls_iteration(elmfb_problem h, const KCtx& c, hipStream_t s) {
                             h->d_w, nullptr, h->d_tpart, st, s)))
     return e;
   if ((e = launch_gather_rows(g, h->d_blocks, h->d_cov, h->d_tpart, ROW_STORE_SQ, h->d_t, nullptr,
-                              st, red1, rw, s)))
-    return e;
-  if ((e = launch_bc_rows(g, h->d_bc, h->d_w, nullptr, ROW_STORE_SQ, h->d_t, nullptr, st,
-                          red1 + rw, s)))
+                              st, red1, rw, h->d_bc, h->d_w, nullptr, s)))
     return e;
   if ((e = launch_cgls_step_a(st, red1, rw + bc_parts(g), s))) return e;
   if ((e = launch_cgls_update_x(g, h->d_x, h->d_w, st, s))) return e;
@@ -140,10 +133,7 @@ hipError_t solve_init(elmfb_problem h, const KCtx& c, int method, const double* 
                               c.A_x, x0, nullptr, h->d_tpart, nullptr, s)))
       return e;
     if ((e = launch_gather_rows(g, h->d_blocks, h->d_cov, h->d_tpart, ROW_RESID, h->d_u, c.rhs,
-                                nullptr, red2, rw, s)))
-      return e;
-    if ((e = launch_bc_rows(g, h->d_bc, x0, nullptr, ROW_RESID, h->d_u, c.rhs, nullptr,
-                            red2 + rw, s)))
+                                nullptr, red2, rw, h->d_bc, x0, nullptr, s)))
       return e;
     n2 = rw + bc_parts(g);
   } else {
