@@ -178,6 +178,9 @@ struct SolveState {
   double target;           // rel-L2 target (0: off)
   int32_t itn, istop, done, iter_lim;
   int32_t target_hit;      // the rel-L2 check met the target
+  // values of this step that workgroups of the kernel forming them still read the old ones of:
+  // the next kernel moves them over (LSQR's alpha, sv and rhobar; CG's gamma)
+  double next_alpha, next_sv, next_rhobar, next_gamma;
   int32_t pad_;
 };
 

@@ -90,6 +90,39 @@ __device__ __forceinline__ double block_sum256(double v, double* sh /* >= 4 doub
   return r;
 }
 
+// Sum of n partials in a fixed order by one workgroup of 256 threads (valid in thread 0).
+__device__ __forceinline__ double reduce_partials(const double* __restrict__ red, int n,
+                                                  double* sh /* >= 4 doubles */) {
+  double v = 0.0;
+  for (int i = threadIdx.x; i < n; i += 256) v += red[i];
+  return block_sum256(v, sh);
+}
+
+// The same sum in every thread of the workgroup (sh: >= 5 doubles).
+__device__ __forceinline__ double reduce_partials_all(const double* __restrict__ red, int n,
+                                                      double* sh) {
+  const double v = reduce_partials(red, n, sh);
+  if (threadIdx.x == 0) sh[4] = v;
+  __syncthreads();
+  return sh[4];
+}
+
+// The same with *done of before the sum, one value for the whole workgroup although another
+// workgroup may set it meanwhile (sh: >= 6 doubles).
+__device__ __forceinline__ double reduce_partials_live(const double* __restrict__ red, int n,
+                                                       const int32_t* done, double* sh,
+                                                       bool* live) {
+  const bool d = threadIdx.x == 0 && *done;
+  const double v = reduce_partials(red, n, sh);
+  if (threadIdx.x == 0) {
+    sh[4] = v;
+    sh[5] = d ? 0.0 : 1.0;
+  }
+  __syncthreads();
+  *live = sh[5] != 0.0;
+  return sh[4];
+}
+
 // Sum 8 per-lane values over the 64 lanes of a wavefront with a transposing butterfly: after
 // the exchanges across lanes 32, 16 and 8 apart each lane holds one of the 8 features (index
 // 4*b5 + 2*b4 + b3 of its lane bits), then three plain steps finish the sums; 10 shuffles for

@@ -268,6 +268,11 @@ __device__ __forceinline__ void rmv_features(const void* __restrict__ A, const i
 // the chunk.  FEW: also loops over only the live groups (blocks that fill part of their chunk);
 // their extra copies of the loop take 96 instead of 60 registers in FP64, which a grid that fills
 // the chip pays for (345 against 341 us on the 3-level problem), so it keeps the one loop.
+// With red, u is LSQR's new u = A v - alpha u, of which red holds the n_red partial squared norms:
+// every workgroup sums them (in one order) to beta = ||u|| and scales u by 1/beta as it reads, and
+// the first one records beta, su = 1/beta, anorm = sqrt(anorm^2 + alpha^2 + beta^2) and hist (may
+// be NULL: beta_{i+1} of step i = itn + 1).  The sums' latency is hidden behind the loads of u;
+// a kernel of its own for beta was about 4.7 us of every step, whatever the problem's size.
 template <int PREC, int VEC, bool FEW>
 __global__ void __launch_bounds__(256) k_rmv_chunks(Geo g, const DevBlock* __restrict__ blocks,
                                                     const Tile* __restrict__ chunks,
@@ -275,7 +280,9 @@ __global__ void __launch_bounds__(256) k_rmv_chunks(Geo g, const DevBlock* __res
                                                     const double* __restrict__ u,
                                                     const double* __restrict__ uscale,
                                                     double* __restrict__ part, int kper,
-                                                    const SolveState* __restrict__ st) {
+                                                    SolveState* st,
+                                                    const double* __restrict__ red, int n_red,
+                                                    double* hist) {
   constexpr int NG = kChunkPts / (256 * VEC);
   static_assert(NG * 256 * VEC == kChunkPts, "chunk size");
   __shared__ double sred[4][264];
@@ -284,7 +291,6 @@ __global__ void __launch_bounds__(256) k_rmv_chunks(Geo g, const DevBlock* __res
   const Tile c = chunks[ci];
   const DevBlock B = blocks[c.blk];
   const int K = g.K;
-  const double sc = uscale ? *uscale : 1.0;
   const int live = (min(B.n - c.p0, kChunkPts) + 256 * VEC - 1) / (256 * VEC);
   double uv[NG][VEC];
   int64_t idx[NG];
@@ -300,12 +306,32 @@ __global__ void __launch_bounds__(256) k_rmv_chunks(Geo g, const DevBlock* __res
       if (p < B.n) {
         const int lx = p / B.ny, ly = p - lx * B.ny;
         const int64_t r = (int64_t)(B.ix0 + lx) * g.ny + (B.iy0 + ly);
-        uv[i][q] = u[r] * sc;
+        uv[i][q] = u[r];
       } else {
         uv[i][q] = 0.0;
       }
     }
   }
+  double sc = uscale ? *uscale : 1.0;
+  if (red) {
+    const double beta = sqrt(reduce_partials_all(red, n_red, &sred[0][0]));
+    sc = beta > 0.0 ? 1.0 / beta : st->su;   // beta = 0: su and anorm stay as they are
+    __syncthreads();                         // sred is used again below
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+      const int step = st->itn + 1;
+      if (hist && step < kHistCap) hist[2 * step + 1] = beta;
+      st->beta = beta;
+      if (beta > 0.0) {
+        st->su = sc;
+        const double a = st->alpha;
+        st->anorm = sqrt(st->anorm * st->anorm + a * a + beta * beta);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NG; ++i)
+#pragma unroll
+    for (int q = 0; q < VEC; ++q) uv[i][q] *= sc;
   const int k0 = blockIdx.y * kper, k1 = min(k0 + kper, K);
   if constexpr (!FEW) rmv_features<PREC, VEC, NG>(A, idx, uv, B.ld, K, k0, k1, sred);
   else if (live <= NG / 8) rmv_features<PREC, VEC, (NG + 7) / 8>(A, idx, uv, B.ld, K, k0, k1, sred);
@@ -533,29 +559,36 @@ hipError_t launch_gather_rows(const Geo& g, const DevBlock* blocks, const int32_
 template <int PREC>
 static void rmv_launch(const Geo& g, const DevBlock* blocks, const Tile* chunks, int64_t n_chunks,
                        const void* A, const double* u, const double* uscale, double* part,
-                       const SolveState* st, hipStream_t s) {
+                       SolveState* st, const double* red, int n_red, double* hist,
+                       hipStream_t s) {
   const int k8 = (g.K + 7) / 8;
   const int split = (int)std::max<int64_t>(1, std::min<int64_t>(k8, kChunkWgs / n_chunks));
   const int kper = 8 * ((k8 + split - 1) / split);
   const dim3 grid((unsigned)n_chunks, (unsigned)((g.K + kper - 1) / kper));
   if (n_chunks < kChunkWgs)
     hipLaunchKernelGGL((k_rmv_chunks<PREC, MvShape<PREC>::vec, true>), grid, dim3(256), 0, s, g,
-                       blocks, chunks, A, u, uscale, part, kper, st);
+                       blocks, chunks, A, u, uscale, part, kper, st, red, n_red, hist);
   else
     hipLaunchKernelGGL((k_rmv_chunks<PREC, MvShape<PREC>::vec, false>), grid, dim3(256), 0, s, g,
-                       blocks, chunks, A, u, uscale, part, kper, st);
+                       blocks, chunks, A, u, uscale, part, kper, st, red, n_red, hist);
 }
 
 hipError_t launch_rmv_chunks(const Geo& g, int prec, const DevBlock* blocks, const Tile* chunks,
                              int64_t n_chunks, const void* A, const double* u,
-                             const double* uscale, double* part, const SolveState* st,
-                             hipStream_t s) {
+                             const double* uscale, double* part, SolveState* st,
+                             const double* red, int n_red, double* hist, hipStream_t s) {
   if (n_chunks == 0) return hipSuccess;
-  if (prec == ELMFB_FP32) rmv_launch<ELMFB_FP32>(g, blocks, chunks, n_chunks, A, u, uscale, part, st, s);
-  else if (prec == ELMFB_BF16) rmv_launch<ELMFB_BF16>(g, blocks, chunks, n_chunks, A, u, uscale, part, st, s);
-  else if (prec == ELMFB_FP16) rmv_launch<ELMFB_FP16>(g, blocks, chunks, n_chunks, A, u, uscale, part, st, s);
-  else rmv_launch<ELMFB_FP64>(g, blocks, chunks, n_chunks, A, u, uscale, part, st, s);
+  if (prec == ELMFB_FP32) rmv_launch<ELMFB_FP32>(g, blocks, chunks, n_chunks, A, u, uscale, part, st, red, n_red, hist, s);
+  else if (prec == ELMFB_BF16) rmv_launch<ELMFB_BF16>(g, blocks, chunks, n_chunks, A, u, uscale, part, st, red, n_red, hist, s);
+  else if (prec == ELMFB_FP16) rmv_launch<ELMFB_FP16>(g, blocks, chunks, n_chunks, A, u, uscale, part, st, red, n_red, hist, s);
+  else rmv_launch<ELMFB_FP64>(g, blocks, chunks, n_chunks, A, u, uscale, part, st, red, n_red, hist, s);
   return hipGetLastError();
+}
+hipError_t launch_rmv_chunks(const Geo& g, int prec, const DevBlock* blocks, const Tile* chunks,
+                             int64_t n_chunks, const void* A, const double* u,
+                             const double* uscale, double* part, SolveState* st, hipStream_t s) {
+  return launch_rmv_chunks(g, prec, blocks, chunks, n_chunks, A, u, uscale, part, st, nullptr, 0,
+                           nullptr, s);
 }
 
 hipError_t launch_rmv_finish(const Geo& g, const int32_t* chunk_start, const double* part,

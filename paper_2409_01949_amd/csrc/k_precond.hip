@@ -25,14 +25,19 @@ __device__ __forceinline__ int bj_tasks(const Geo& g) {
   return g.n_blocks * ((g.K + kBjRows - 1) / kBjRows);
 }
 
-// y = R^{-1} (v * scale):  y_i = sum_{k >= i} Ri[i][k] v_k = sum_k T[k][i] v_k
+// y = R^{-1} (v * scale):  y_i = sum_{k >= i} Ri[i][k] v_k = sum_k T[k][i] v_k; with red (may be
+// NULL) also the partials of r . y.
 __global__ void __launch_bounds__(256) k_bj_apply(Geo g, const double* __restrict__ rinvT,
                                                   const double* __restrict__ v,
                                                   const double* __restrict__ scale,
                                                   double* __restrict__ y,
-                                                  const SolveState* __restrict__ st) {
+                                                  const SolveState* __restrict__ st,
+                                                  const double* __restrict__ r,
+                                                  double* __restrict__ red) {
   __shared__ double part[kBjSplit][kBjRows];
+  __shared__ double sh[4];
   if (st && st->done) return;
+  double acc = 0.0;
   const int K = g.K;
   const int per = (K + kBjRows - 1) / kBjRows;
   const double sc = scale ? *scale : 1.0;
@@ -51,8 +56,13 @@ __global__ void __launch_bounds__(256) k_bj_apply(Geo g, const double* __restric
 #pragma unroll
       for (int q = 0; q < kBjSplit; ++q) t += part[q][ro];
       y[q0 + i] = t * sc;
+      if (red) acc += r[q0 + i] * (t * sc);
     }
     __syncthreads();
+  }
+  if (red) {
+    const double t = block_sum256(acc, sh);
+    if (threadIdx.x == 0) red[blockIdx.x] = t;
   }
 }
 
@@ -142,8 +152,9 @@ int bj_wg(const Geo& g) {
 }
 
 hipError_t launch_bj_apply(const Geo& g, const double* rinvT, const double* v,
-                           const double* scale, double* y, const SolveState* st, hipStream_t s) {
-  hipLaunchKernelGGL(k_bj_apply, dim3(bj_wg(g)), dim3(256), 0, s, g, rinvT, v, scale, y, st);
+                           const double* scale, double* y, const SolveState* st, const double* r,
+                           double* red, hipStream_t s) {
+  hipLaunchKernelGGL(k_bj_apply, dim3(bj_wg(g)), dim3(256), 0, s, g, rinvT, v, scale, y, st, r, red);
   return hipGetLastError();
 }
 hipError_t launch_bj_apply_t(const Geo& g, const double* rinv, const double* x, int mode,

@@ -9,12 +9,10 @@
 
 namespace elmfb {
 
-// Sum of n partials in a fixed order by one workgroup of 256 threads (valid in thread 0).
-__device__ double reduce_partials(const double* __restrict__ red, int n, double* sh) {
-  double v = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) v += red[i];
-  return block_sum256(v, sh);
-}
+// A kernel of a few workgroups takes about 4.7 us of a step whatever it does (dispatch and the
+// wait for the one before), so the scalars are formed where they are used: every workgroup of the
+// kernel that needs one sums its partials, in one order, and the first records it.  A value whose
+// old one the others still read goes to a next_ field, which the following kernel moves over.
 
 __global__ void __launch_bounds__(256) k_sumsq(const double* __restrict__ x, int64_t n,
                                                double* __restrict__ red) {
@@ -108,67 +106,40 @@ __global__ void k_init_xw(Geo g, const double* __restrict__ x0, double* __restri
   }
 }
 
-// beta = ||A v - alpha u||; su = 1/beta; anorm = sqrt(anorm^2 + alpha^2 + beta^2).
-// hist (may be NULL) receives beta_{i+1} of step i = itn + 1.
-__global__ void __launch_bounds__(256) k_lsqr_beta(SolveState* st, const double* red, int n,
-                                                   double* hist) {
-  __shared__ double sh[4];
-  if (st->done) return;
-  const double s = reduce_partials(red, n, sh);
-  if (threadIdx.x == 0) {
-    const double beta = sqrt(s);
-    st->beta = beta;
-    const int i = st->itn + 1;
-    if (hist && i < kHistCap) hist[2 * i + 1] = beta;
-    if (beta > 0.0) {
-      st->su = 1.0 / beta;
-      const double a = st->alpha;
-      st->anorm = sqrt(st->anorm * st->anorm + a * a + beta * beta);
-    }
-  }
-}
-
-// alpha = ||A^T u - beta v||, sv = 1/alpha, then the plane rotation of this step.
+// alpha = ||A^T u - beta v|| from its n partials, sv = 1/alpha, the plane rotation of this step,
+// then x += t1 w ; w = v/alpha + t2 w ; partial ||x||^2.
 // hist (may be NULL) receives alpha_{i+1} of step i = itn + 1.
-__global__ void __launch_bounds__(256) k_lsqr_alpha(SolveState* st, const double* red, int n,
-                                                    double* hist) {
-  __shared__ double sh[4];
-  if (st->done) return;
-  const double s = reduce_partials(red, n, sh);
-  if (threadIdx.x == 0) {
-    const double beta = st->beta;
-    double alpha = st->alpha;
-    if (beta > 0.0) {
-      alpha = sqrt(s);
-      st->alpha = alpha;
-      if (alpha > 0.0) st->sv = 1.0 / alpha;
-    }
-    const int i = st->itn + 1;
-    if (hist && i < kHistCap) hist[2 * i] = alpha;
-    const double rhobar = st->rhobar;
-    const double rho = sqrt(rhobar * rhobar + beta * beta);
-    const double c = rhobar / rho, sn = beta / rho;
-    const double theta = sn * alpha;
-    st->rhobar = -c * alpha;
-    const double phi = c * st->phibar;
-    const double phibar = sn * st->phibar;
-    st->phibar = phibar;
-    st->t1 = phi / rho;
-    st->t2 = -theta / rho;
-    st->rnorm = phibar;
-    st->arnorm = alpha * fabs(c) * phibar;
-  }
-}
-
-// x += t1 w ; w = v/alpha + t2 w ; partial ||x||^2.
 __global__ void __launch_bounds__(256) k_lsqr_update(Geo g, double* __restrict__ x,
                                                      double* __restrict__ w,
-                                                     const double* __restrict__ v,
-                                                     const SolveState* __restrict__ st,
-                                                     double* __restrict__ red) {
-  __shared__ double sh[4];
+                                                     const double* __restrict__ v, SolveState* st,
+                                                     const double* __restrict__ red_v, int n,
+                                                     double* hist, double* __restrict__ red) {
+  __shared__ double sh[5];
   if (st->done) return;
-  const double t1 = st->t1, t2 = st->t2, sv = st->sv;
+  const double beta = st->beta, rhobar = st->rhobar, phibar0 = st->phibar;
+  double alpha = st->alpha, sv = st->sv;
+  const double s = reduce_partials_all(red_v, n, sh);
+  if (beta > 0.0) {
+    alpha = sqrt(s);
+    if (alpha > 0.0) sv = 1.0 / alpha;
+  }
+  const double rho = sqrt(rhobar * rhobar + beta * beta);
+  const double c = rhobar / rho, sn = beta / rho;
+  const double theta = sn * alpha;
+  const double phi = c * phibar0;
+  const double phibar = sn * phibar0;
+  const double t1 = phi / rho, t2 = -theta / rho;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    const int i = st->itn + 1;
+    if (hist && i < kHistCap) hist[2 * i] = alpha;
+    st->next_alpha = alpha;
+    st->next_sv = sv;
+    st->next_rhobar = -c * alpha;
+    st->t1 = t1;
+    st->t2 = t2;
+    st->rnorm = phibar;   // and the next phibar
+    st->arnorm = alpha * fabs(c) * phibar;
+  }
   double acc = 0.0;
   for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < g.n_phi;
        q += (int64_t)gridDim.x * blockDim.x) {
@@ -178,11 +149,13 @@ __global__ void __launch_bounds__(256) k_lsqr_update(Geo g, double* __restrict__
     w[q] = v[q] * sv + t2 * wq;
     acc += xq * xq;
   }
-  const double s = block_sum256(acc, sh);
-  if (threadIdx.x == 0) red[blockIdx.x] = s;
+  __syncthreads();   // sh is used again
+  const double t = block_sum256(acc, sh);
+  if (threadIdx.x == 0) red[blockIdx.x] = t;
 }
 
-// Paige-Saunders stopping tests (conlim off).
+// The end of a step: its values become the current ones, then the Paige-Saunders stopping tests
+// (conlim off).
 __global__ void __launch_bounds__(256) k_lsqr_stop(SolveState* st, const double* red, int n) {
   __shared__ double sh[4];
   if (st->done) return;
@@ -192,6 +165,10 @@ __global__ void __launch_bounds__(256) k_lsqr_stop(SolveState* st, const double*
     const double xnorm = sqrt(s);
     st->xnorm = xnorm;
     st->itn += 1;
+    st->alpha = st->next_alpha;
+    st->sv = st->next_sv;
+    st->rhobar = st->next_rhobar;
+    st->phibar = st->rnorm;
     const double anorm = st->anorm, rnorm = st->rnorm, bnorm = st->bnorm;
     const double test1 = rnorm / bnorm;
     const double test2 = st->arnorm / (anorm * rnorm + eps);
@@ -218,7 +195,7 @@ __global__ void __launch_bounds__(256) k_cgls_init(SolveState* st, const double*
   if (threadIdx.x == 0) {
     st->bnorm = sqrt(sb);
     st->rnorm = sqrt(sr);
-    st->gamma = ss;
+    st->gamma = st->next_gamma = ss;
     st->arnorm = sqrt(ss);
     st->anorm = anorm_f;
     st->itn = 0;
@@ -230,66 +207,65 @@ __global__ void __launch_bounds__(256) k_cgls_init(SolveState* st, const double*
   }
 }
 
-__global__ void __launch_bounds__(256) k_cgls_step_a(SolveState* st, const double* red, int n) {
-  __shared__ double sh[4];
+// cg_a = gamma / ||A p||^2 from its n partials, then x += cg_a p ; r -= cg_a t (t = A p) ; partial
+// ||r||^2.
+__global__ void __launch_bounds__(256) k_cgls_update(Geo g, double* __restrict__ x,
+                                                     const double* __restrict__ p,
+                                                     double* __restrict__ r,
+                                                     const double* __restrict__ t, SolveState* st,
+                                                     const double* __restrict__ red_t, int n,
+                                                     double* __restrict__ red) {
+  __shared__ double sh[5];
   if (st->done) return;
-  const double s = reduce_partials(red, n, sh);
-  if (threadIdx.x == 0) st->cg_a = st->gamma / s;
-}
-
-__global__ void k_cgls_update_x(Geo g, double* __restrict__ x, const double* __restrict__ p,
-                                const SolveState* __restrict__ st) {
-  if (st->done) return;
-  const double a = st->cg_a;
-  for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < g.n_phi;
-       q += (int64_t)gridDim.x * blockDim.x)
-    x[q] = x[q] + a * p[q];
-}
-
-__global__ void __launch_bounds__(256) k_cgls_update_r(Geo g, double* __restrict__ r,
-                                                       const double* __restrict__ t,
-                                                       const SolveState* __restrict__ st,
-                                                       double* __restrict__ red) {
-  __shared__ double sh[4];
-  if (st->done) return;
-  const double a = st->cg_a;
+  const double gamma = st->next_gamma;
+  const double a = gamma / reduce_partials_all(red_t, n, sh);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->cg_a = a;
+    st->gamma = gamma;
+  }
+  const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t q = i0; q < g.n_phi; q += step) x[q] = x[q] + a * p[q];
   double acc = 0.0;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < g.n_rows + g.n_bc;
-       i += (int64_t)gridDim.x * blockDim.x) {
+  for (int64_t i = i0; i < g.n_rows + g.n_bc; i += step) {
     const double v = r[i] - a * t[i];
     r[i] = v;
     acc += v * v;
   }
+  __syncthreads();   // sh is used again
   const double s = block_sum256(acc, sh);
   if (threadIdx.x == 0) red[blockIdx.x] = s;
 }
 
-__global__ void __launch_bounds__(256) k_cgls_step_b(SolveState* st, const double* red_r, int nr,
-                                                     const double* red_s, int ns) {
-  __shared__ double sh[4];
-  if (st->done) return;
-  const double sr = reduce_partials(red_r, nr, sh);
-  const double ss = reduce_partials(red_s, ns, sh);
-  if (threadIdx.x == 0) {
-    st->cg_b = ss / st->gamma;
-    st->gamma = ss;
-    const double rnorm = sqrt(sr);
-    st->rnorm = rnorm;
-    st->arnorm = sqrt(ss);
-    st->itn += 1;
-    int istop = 0;
-    if (sqrt(ss) <= st->atol * st->anorm * rnorm) istop = 2;
-    if (rnorm <= st->btol * st->bnorm) istop = 1;
-    if (istop == 0 && st->itn >= st->iter_lim) istop = 7;
-    if (istop != 0) { st->istop = istop; st->done = 1; }
+// The end of a step: ||r||, gamma = ||s||^2, cg_b, the stopping tests, and p = s + cg_b p (p is not
+// used after the step that stopped).
+__global__ void __launch_bounds__(256) k_cgls_update_p(Geo g, double* __restrict__ p,
+                                                       const double* __restrict__ s,
+                                                       SolveState* st,
+                                                       const double* __restrict__ red_r, int nr,
+                                                       const double* __restrict__ red_s, int ns) {
+  __shared__ double sh[6];
+  bool live;
+  const double ss = reduce_partials_live(red_s, ns, &st->done, sh, &live);
+  if (!live) return;
+  const double b = ss / st->gamma;
+  if (blockIdx.x == 0) {   // the whole workgroup: a sum follows
+    __syncthreads();
+    const double sr = reduce_partials(red_r, nr, sh);
+    if (threadIdx.x == 0) {
+      st->cg_b = b;
+      st->next_gamma = ss;
+      const double rnorm = sqrt(sr);
+      st->rnorm = rnorm;
+      st->arnorm = sqrt(ss);
+      st->itn += 1;
+      int istop = 0;
+      if (sqrt(ss) <= st->atol * st->anorm * rnorm) istop = 2;
+      if (rnorm <= st->btol * st->bnorm) istop = 1;
+      if (istop == 0 && st->itn >= st->iter_lim) istop = 7;
+      if (istop != 0) { st->istop = istop; st->done = 1; }
+    }
   }
-}
-
-// p = s + b p   (runs even on the step that stopped: p is not used afterwards)
-__global__ void k_cgls_update_p(Geo g, double* __restrict__ p, const double* __restrict__ s,
-                                const SolveState* __restrict__ st) {
-  const double b = st->cg_b;
-  if (st->done) return;
   for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < g.n_phi;
        q += (int64_t)gridDim.x * blockDim.x)
     p[q] = s[q] + b * p[q];
@@ -350,19 +326,11 @@ hipError_t launch_init_xw(const Geo& g, const double* x0, double* x, double* w, 
   hipLaunchKernelGGL(k_init_xw, grid_for(g.n_phi), dim3(256), 0, s, g, x0, x, w, v, st);
   return hipGetLastError();
 }
-hipError_t launch_lsqr_beta(SolveState* st, const double* red, int n, double* hist,
-                            hipStream_t s) {
-  hipLaunchKernelGGL(k_lsqr_beta, dim3(1), dim3(256), 0, s, st, red, n, hist);
-  return hipGetLastError();
-}
-hipError_t launch_lsqr_alpha(SolveState* st, const double* red, int n, double* hist,
-                             hipStream_t s) {
-  hipLaunchKernelGGL(k_lsqr_alpha, dim3(1), dim3(256), 0, s, st, red, n, hist);
-  return hipGetLastError();
-}
-hipError_t launch_lsqr_update(const Geo& g, double* x, double* w, const double* v,
-                              const SolveState* st, double* red, int n_wg, hipStream_t s) {
-  hipLaunchKernelGGL(k_lsqr_update, dim3(n_wg), dim3(256), 0, s, g, x, w, v, st, red);
+hipError_t launch_lsqr_update(const Geo& g, double* x, double* w, const double* v, SolveState* st,
+                              const double* red_v, int n_red, double* hist, double* red, int n_wg,
+                              hipStream_t s) {
+  hipLaunchKernelGGL(k_lsqr_update, dim3(n_wg), dim3(256), 0, s, g, x, w, v, st, red_v, n_red,
+                     hist, red);
   return hipGetLastError();
 }
 hipError_t launch_lsqr_stop(SolveState* st, const double* red, int n, hipStream_t s) {
@@ -383,28 +351,18 @@ hipError_t launch_copy(const double* src, double* dst, int64_t n, hipStream_t s)
   hipLaunchKernelGGL(k_copy, grid_for(n), dim3(256), 0, s, src, dst, n);
   return hipGetLastError();
 }
-hipError_t launch_cgls_step_a(SolveState* st, const double* red, int n, hipStream_t s) {
-  hipLaunchKernelGGL(k_cgls_step_a, dim3(1), dim3(256), 0, s, st, red, n);
+hipError_t launch_cgls_update(const Geo& g, double* x, const double* p, double* r, const double* t,
+                              SolveState* st, const double* red_t, int n_red, double* red, int n_wg,
+                              hipStream_t s) {
+  hipLaunchKernelGGL(k_cgls_update, dim3(n_wg), dim3(256), 0, s, g, x, p, r, t, st, red_t, n_red,
+                     red);
   return hipGetLastError();
 }
-hipError_t launch_cgls_update_x(const Geo& g, double* x, const double* p, const SolveState* st,
+hipError_t launch_cgls_update_p(const Geo& g, double* p, const double* sv, SolveState* st,
+                                const double* red_r, int nr, const double* red_s, int ns,
                                 hipStream_t s) {
-  hipLaunchKernelGGL(k_cgls_update_x, grid_for(g.n_phi), dim3(256), 0, s, g, x, p, st);
-  return hipGetLastError();
-}
-hipError_t launch_cgls_update_r(const Geo& g, double* r, const double* t, const SolveState* st,
-                                double* red, int n_wg, hipStream_t s) {
-  hipLaunchKernelGGL(k_cgls_update_r, dim3(n_wg), dim3(256), 0, s, g, r, t, st, red);
-  return hipGetLastError();
-}
-hipError_t launch_cgls_step_b(SolveState* st, const double* red_r, int nr, const double* red_s,
-                              int ns, hipStream_t s) {
-  hipLaunchKernelGGL(k_cgls_step_b, dim3(1), dim3(256), 0, s, st, red_r, nr, red_s, ns);
-  return hipGetLastError();
-}
-hipError_t launch_cgls_update_p(const Geo& g, double* p, const double* sv, const SolveState* st,
-                                hipStream_t s) {
-  hipLaunchKernelGGL(k_cgls_update_p, grid_for(g.n_phi), dim3(256), 0, s, g, p, sv, st);
+  hipLaunchKernelGGL(k_cgls_update_p, grid_for(g.n_phi), dim3(256), 0, s, g, p, sv, st, red_r, nr,
+                     red_s, ns);
   return hipGetLastError();
 }
 
@@ -424,7 +382,7 @@ __global__ void __launch_bounds__(256) k_gcg_init(SolveState* st, const double* 
   if (threadIdx.x == 0) {
     st->bnorm = sqrt(bb);
     st->rnorm = sqrt(rr);
-    st->gamma = rz;
+    st->gamma = st->next_gamma = rz;
     st->cg_a = st->cg_b = 0.0;
     st->itn = 0;
     st->istop = 0;
@@ -435,33 +393,31 @@ __global__ void __launch_bounds__(256) k_gcg_init(SolveState* st, const double* 
   }
 }
 
-// cg_a = gamma / (p . q); a breakdown (p . q <= 0: G not positive definite in this precision)
-// stops with istop 3.
-__global__ void __launch_bounds__(256) k_gcg_alpha(SolveState* st, const double* red, int n) {
-  __shared__ double sh[4];
-  if (st->done) return;
-  const double pq = reduce_partials(red, n, sh);
-  if (threadIdx.x == 0) {
-    if (pq > 0.0) {
-      st->cg_a = st->gamma / pq;
-    } else {
-      st->cg_a = 0.0;
+// cg_a = gamma / (p . q) from the n partials of p . q, then a += cg_a p ; r -= cg_a q ; partial
+// r . r.  A breakdown (p . q <= 0: G not positive definite in this precision) stops with istop 3;
+// a workgroup that reads that `done` already has nothing to do either.
+__global__ void __launch_bounds__(256) k_gcg_update(Geo g, double* __restrict__ a,
+                                                    double* __restrict__ r,
+                                                    const double* __restrict__ p,
+                                                    const double* __restrict__ q, SolveState* st,
+                                                    const double* __restrict__ red_pq, int n,
+                                                    double* __restrict__ red) {
+  __shared__ double sh[6];
+  bool live;
+  const double gamma = st->next_gamma;
+  const double pq = reduce_partials_live(red_pq, n, &st->done, sh, &live);
+  if (!live) return;
+  const bool ok = pq > 0.0;
+  const double al = ok ? gamma / pq : 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->cg_a = al;
+    st->gamma = gamma;
+    if (!ok) {
       st->istop = 3;
       st->done = 1;
     }
   }
-}
-
-// a += cg_a p ; r -= cg_a q ; partial r . r.
-__global__ void __launch_bounds__(256) k_gcg_update(Geo g, double* __restrict__ a,
-                                                    double* __restrict__ r,
-                                                    const double* __restrict__ p,
-                                                    const double* __restrict__ q,
-                                                    const SolveState* __restrict__ st,
-                                                    double* __restrict__ red) {
-  __shared__ double sh[4];
-  if (st->done) return;
-  const double al = st->cg_a;
+  if (!ok) return;
   double acc = 0.0;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < g.n_phi;
        t += (int64_t)gridDim.x * blockDim.x) {
@@ -470,17 +426,16 @@ __global__ void __launch_bounds__(256) k_gcg_update(Geo g, double* __restrict__ 
     r[t] = rt;
     acc += rt * rt;
   }
+  __syncthreads();   // sh is used again
   const double sum = block_sum256(acc, sh);
   if (threadIdx.x == 0) red[blockIdx.x] = sum;
 }
 
-// partial x . y (skipped once the solve is done; st may be NULL).
+// partial x . y.
 __global__ void __launch_bounds__(256) k_dot(const double* __restrict__ x,
                                              const double* __restrict__ y, int64_t n,
-                                             const SolveState* __restrict__ st,
                                              double* __restrict__ red) {
   __shared__ double sh[4];
-  if (st && st->done) return;
   double acc = 0.0;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n;
        t += (int64_t)gridDim.x * blockDim.x)
@@ -489,34 +444,37 @@ __global__ void __launch_bounds__(256) k_dot(const double* __restrict__ x,
   if (threadIdx.x == 0) red[blockIdx.x] = sum;
 }
 
-// rnorm = ||r||, gamma' = r.z, cg_b = gamma'/gamma; stop on ||r|| <= btol ||g|| (istop 1) or
-// the iteration limit (istop 7).
-__global__ void __launch_bounds__(256) k_gcg_beta(SolveState* st, const double* red_r, int nr,
-                                                  const double* red_z, int nz) {
-  __shared__ double sh[4];
-  if (st->done) return;
-  const double rr = reduce_partials(red_r, nr, sh);
-  const double rz = red_z ? reduce_partials(red_z, nz, sh) : rr;
-  if (threadIdx.x == 0) {
-    st->itn += 1;
-    st->rnorm = sqrt(rr);
-    st->cg_b = st->gamma > 0.0 ? rz / st->gamma : 0.0;
-    st->gamma = rz;
-    int istop = 0;
-    if (st->rnorm <= st->btol * st->bnorm) istop = 1;
-    else if (st->itn >= st->iter_lim) istop = 7;
-    if (istop) { st->istop = istop; st->done = 1; }
+// The end of a step: rnorm = ||r||, gamma' = r.z (its partials red_z; NULL: z = r), cg_b =
+// gamma'/gamma, stop on ||r|| <= btol ||g|| (istop 1) or the iteration limit (istop 7), and
+// p = z + cg_b p (p is not used after the step that stopped).
+__global__ void __launch_bounds__(256) k_gcg_pupdate(Geo g, double* __restrict__ p,
+                                                     const double* __restrict__ z, SolveState* st,
+                                                     const double* __restrict__ red_r, int nr,
+                                                     const double* __restrict__ red_z, int nz) {
+  __shared__ double sh[6];
+  bool live;
+  const double rz = reduce_partials_live(red_z ? red_z : red_r, red_z ? nz : nr, &st->done, sh,
+                                         &live);
+  if (!live) return;
+  const double gamma = st->gamma;
+  const double b = gamma > 0.0 ? rz / gamma : 0.0;
+  if (blockIdx.x == 0) {   // the whole workgroup: a sum follows
+    __syncthreads();
+    const double rr = reduce_partials(red_r, nr, sh);
+    if (threadIdx.x == 0) {
+      st->itn += 1;
+      st->rnorm = sqrt(rr);
+      st->cg_b = b;
+      st->next_gamma = rz;
+      int istop = 0;
+      if (st->rnorm <= st->btol * st->bnorm) istop = 1;
+      else if (st->itn >= st->iter_lim) istop = 7;
+      if (istop) { st->istop = istop; st->done = 1; }
+    }
   }
-}
-
-// p = z + cg_b p (p = z at the start: cg_b = 0 with init = 1).
-__global__ void k_gcg_pupdate(Geo g, double* __restrict__ p, const double* __restrict__ z,
-                              const SolveState* __restrict__ st, int init) {
-  if (!init && st->done) return;
-  const double b = init ? 0.0 : st->cg_b;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < g.n_phi;
        t += (int64_t)gridDim.x * blockDim.x)
-    p[t] = z[t] + (init ? 0.0 : b * p[t]);
+    p[t] = z[t] + b * p[t];
 }
 
 hipError_t launch_gcg_init(SolveState* st, const double* red_b, int nb, const double* red_r,
@@ -524,28 +482,23 @@ hipError_t launch_gcg_init(SolveState* st, const double* red_b, int nb, const do
   hipLaunchKernelGGL(k_gcg_init, dim3(1), dim3(256), 0, s, st, red_b, nb, red_r, nr, red_z, nz);
   return hipGetLastError();
 }
-hipError_t launch_gcg_alpha(SolveState* st, const double* red, int n, hipStream_t s) {
-  hipLaunchKernelGGL(k_gcg_alpha, dim3(1), dim3(256), 0, s, st, red, n);
-  return hipGetLastError();
-}
 hipError_t launch_gcg_update(const Geo& g, double* a, double* r, const double* p, const double* q,
-                             const SolveState* st, double* red, int n_wg, hipStream_t s) {
-  hipLaunchKernelGGL(k_gcg_update, dim3(n_wg), dim3(256), 0, s, g, a, r, p, q, st, red);
+                             SolveState* st, const double* red_pq, int n_red, double* red, int n_wg,
+                             hipStream_t s) {
+  hipLaunchKernelGGL(k_gcg_update, dim3(n_wg), dim3(256), 0, s, g, a, r, p, q, st, red_pq, n_red,
+                     red);
   return hipGetLastError();
 }
-hipError_t launch_dot(const double* x, const double* y, int64_t n, const SolveState* st,
-                      double* red, int n_wg, hipStream_t s) {
-  hipLaunchKernelGGL(k_dot, dim3(n_wg), dim3(256), 0, s, x, y, n, st, red);
+hipError_t launch_dot(const double* x, const double* y, int64_t n, double* red, int n_wg,
+                      hipStream_t s) {
+  hipLaunchKernelGGL(k_dot, dim3(n_wg), dim3(256), 0, s, x, y, n, red);
   return hipGetLastError();
 }
-hipError_t launch_gcg_beta(SolveState* st, const double* red_r, int nr, const double* red_z,
-                           int nz, hipStream_t s) {
-  hipLaunchKernelGGL(k_gcg_beta, dim3(1), dim3(256), 0, s, st, red_r, nr, red_z, nz);
-  return hipGetLastError();
-}
-hipError_t launch_gcg_pupdate(const Geo& g, double* p, const double* z, const SolveState* st,
-                              int init, hipStream_t s) {
-  hipLaunchKernelGGL(k_gcg_pupdate, grid_for(g.n_phi), dim3(256), 0, s, g, p, z, st, init);
+hipError_t launch_gcg_pupdate(const Geo& g, double* p, const double* z, SolveState* st,
+                              const double* red_r, int nr, const double* red_z, int nz,
+                              hipStream_t s) {
+  hipLaunchKernelGGL(k_gcg_pupdate, grid_for(g.n_phi), dim3(256), 0, s, g, p, z, st, red_r, nr,
+                     red_z, nz);
   return hipGetLastError();
 }
 

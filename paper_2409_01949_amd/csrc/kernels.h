@@ -44,8 +44,13 @@ hipError_t launch_gather_rows(const Geo& g, const DevBlock* blocks, const int32_
 // stage 1 of x = A^T u: per chunk partial dot products [n_chunks][K]
 hipError_t launch_rmv_chunks(const Geo& g, int prec, const DevBlock* blocks, const Tile* chunks,
                              int64_t n_chunks, const void* A, const double* u,
-                             const double* uscale, double* part, const SolveState* st,
-                             hipStream_t s);
+                             const double* uscale, double* part, SolveState* st, hipStream_t s);
+// the same in an LSQR step: u scaled by 1/beta, beta = ||u|| from its n_red norm partials, which
+// this records in st and hist (may be NULL)
+hipError_t launch_rmv_chunks(const Geo& g, int prec, const DevBlock* blocks, const Tile* chunks,
+                             int64_t n_chunks, const void* A, const double* u,
+                             const double* uscale, double* part, SolveState* st,
+                             const double* red, int n_red, double* hist, hipStream_t s);
 // stage 2: x[q] = sum over the block's chunks, then the column epilogue
 hipError_t launch_rmv_finish(const Geo& g, const int32_t* chunk_start, const double* part,
                              int mode, double* out, const SolveState* st, double* red, int n_wg,
@@ -88,24 +93,18 @@ hipError_t launch_lsqr_init_alpha(SolveState* st, const double* red, int n, doub
                                   hipStream_t s);
 hipError_t launch_init_xw(const Geo& g, const double* x0, double* x, double* w, const double* v,
                           const SolveState* st, hipStream_t s);
-hipError_t launch_lsqr_beta(SolveState* st, const double* red, int n, double* hist,
-                            hipStream_t s);
-hipError_t launch_lsqr_alpha(SolveState* st, const double* red, int n, double* hist,
-                             hipStream_t s);
-hipError_t launch_lsqr_update(const Geo& g, double* x, double* w, const double* v,
-                              const SolveState* st, double* red, int n_wg, hipStream_t s);
+hipError_t launch_lsqr_update(const Geo& g, double* x, double* w, const double* v, SolveState* st,
+                              const double* red_v, int n_red, double* hist, double* red, int n_wg,
+                              hipStream_t s);
 hipError_t launch_lsqr_stop(SolveState* st, const double* red, int n, hipStream_t s);
 hipError_t launch_cgls_init(SolveState* st, const double* red_b, int nb, const double* red_r,
                             int nr, const double* red_s, int ns, double anorm_f, hipStream_t s);
 hipError_t launch_copy(const double* src, double* dst, int64_t n, hipStream_t s);
-hipError_t launch_cgls_step_a(SolveState* st, const double* red, int n, hipStream_t s);
-hipError_t launch_cgls_update_x(const Geo& g, double* x, const double* p, const SolveState* st,
-                                hipStream_t s);
-hipError_t launch_cgls_update_r(const Geo& g, double* r, const double* t, const SolveState* st,
-                                double* red, int n_wg, hipStream_t s);
-hipError_t launch_cgls_step_b(SolveState* st, const double* red_r, int nr, const double* red_s,
-                              int ns, hipStream_t s);
-hipError_t launch_cgls_update_p(const Geo& g, double* p, const double* sv, const SolveState* st,
+hipError_t launch_cgls_update(const Geo& g, double* x, const double* p, double* r, const double* t,
+                              SolveState* st, const double* red_t, int n_red, double* red, int n_wg,
+                              hipStream_t s);
+hipError_t launch_cgls_update_p(const Geo& g, double* p, const double* sv, SolveState* st,
+                                const double* red_r, int nr, const double* red_s, int ns,
                                 hipStream_t s);
 hipError_t launch_sumsq_entries(int prec, const void* A, int64_t n, double* red, int n_wg,
                                 hipStream_t s);
@@ -125,15 +124,14 @@ hipError_t launch_gram_mv_pairs_only(const Geo& g, int gram_prec, const GramPair
 // CG on the Gram blocks (FP64 vectors and scalars).
 hipError_t launch_gcg_init(SolveState* st, const double* red_b, int nb, const double* red_r,
                            int nr, const double* red_z, int nz, hipStream_t s);
-hipError_t launch_gcg_alpha(SolveState* st, const double* red, int n, hipStream_t s);
 hipError_t launch_gcg_update(const Geo& g, double* a, double* r, const double* p, const double* q,
-                             const SolveState* st, double* red, int n_wg, hipStream_t s);
-hipError_t launch_dot(const double* x, const double* y, int64_t n, const SolveState* st,
-                      double* red, int n_wg, hipStream_t s);
-hipError_t launch_gcg_beta(SolveState* st, const double* red_r, int nr, const double* red_z,
-                           int nz, hipStream_t s);
-hipError_t launch_gcg_pupdate(const Geo& g, double* p, const double* z, const SolveState* st,
-                              int init, hipStream_t s);
+                             SolveState* st, const double* red_pq, int n_red, double* red, int n_wg,
+                             hipStream_t s);
+hipError_t launch_dot(const double* x, const double* y, int64_t n, double* red, int n_wg,
+                      hipStream_t s);
+hipError_t launch_gcg_pupdate(const Geo& g, double* p, const double* z, SolveState* st,
+                              const double* red_r, int nr, const double* red_z, int nz,
+                              hipStream_t s);
 // points of one load of the Gram kernel (a chunk starts on a multiple of them within a run)
 int gram_load_points(int prec, int K);
 hipError_t launch_gram(const Geo& g, int prec, const DevBlock* blocks, const GramPair* pairs,
@@ -146,8 +144,10 @@ int bj_wg(const Geo& g);
 hipError_t launch_bj_factor(const Geo& g, const double* G, const int64_t* diag_off, double shift,
                             double* work, double* rinv, double* rinvT, int32_t* nfail,
                             hipStream_t s);
+// red (NULL: none): the bj_wg(g) partials of r . y
 hipError_t launch_bj_apply(const Geo& g, const double* rinvT, const double* v,
-                           const double* scale, double* y, const SolveState* st, hipStream_t s);
+                           const double* scale, double* y, const SolveState* st, const double* r,
+                           double* red, hipStream_t s);
 hipError_t launch_bj_apply_t(const Geo& g, const double* rinv, const double* x, int mode,
                              double* out, const SolveState* st, double* red, hipStream_t s);
 hipError_t launch_bj_recover(const Geo& g, const double* rinvT, const double* y, const double* x0,

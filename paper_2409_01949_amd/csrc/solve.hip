@@ -59,7 +59,7 @@ hipError_t lsqr_iteration(elmfb_problem h, const KCtx& c, hipStream_t s) {
   // u = A v / alpha - ... (v scaled by 1/alpha as it is read)
   if (c.apply) {
     if ((e = launch_bj_apply(g, h->d_rinvT, h->d_v, state_field(h, offsetof(SolveState, sv)),
-                             h->d_vt, st, s)))
+                             h->d_vt, st, nullptr, nullptr, s)))
       return e;
     if ((e = launch_mv_blocks(g, c.prec, h->d_blocks, h->d_tiles, nt, c.A, h->d_vt, nullptr,
                               h->d_tpart, st, s)))
@@ -73,9 +73,8 @@ hipError_t lsqr_iteration(elmfb_problem h, const KCtx& c, hipStream_t s) {
                               st, red1, rw, h->d_bc, c.apply ? h->d_vt : h->d_v,
                               c.apply ? nullptr : state_field(h, offsetof(SolveState, sv)), s)))
     return e;
-  if ((e = launch_lsqr_beta(st, red1, rw + bc_parts(g), h->d_hist, s))) return e;
-  if ((e = launch_rmv_chunks(g, c.prec, h->d_blocks, h->d_chunks, nc, c.A, h->d_u,
-                             state_field(h, offsetof(SolveState, su)), h->d_part, st, s)))
+  if ((e = launch_rmv_chunks(g, c.prec, h->d_blocks, h->d_chunks, nc, c.A, h->d_u, nullptr,
+                             h->d_part, st, red1, rw + bc_parts(g), h->d_hist, s)))
     return e;
   int na = cw;
   if (c.apply) {
@@ -88,8 +87,8 @@ hipError_t lsqr_iteration(elmfb_problem h, const KCtx& c, hipStream_t s) {
                                h->d_bc, h->d_u, state_field(h, offsetof(SolveState, su)), s)))
       return e;
   }
-  if ((e = launch_lsqr_alpha(st, red2, na, h->d_hist, s))) return e;
-  if ((e = launch_lsqr_update(g, h->d_x, h->d_w, h->d_v, st, red3, cw, s))) return e;
+  if ((e = launch_lsqr_update(g, h->d_x, h->d_w, h->d_v, st, red2, na, h->d_hist, red3, cw, s)))
+    return e;
   return launch_lsqr_stop(st, red3, cw, s);
 }
 
@@ -105,17 +104,16 @@ hipError_t cgls_iteration(elmfb_problem h, const KCtx& c, hipStream_t s) {
   if ((e = launch_gather_rows(g, h->d_blocks, h->d_cov, h->d_tpart, ROW_STORE_SQ, h->d_t, nullptr,
                               st, red1, rw, h->d_bc, h->d_w, nullptr, s)))
     return e;
-  if ((e = launch_cgls_step_a(st, red1, rw + bc_parts(g), s))) return e;
-  if ((e = launch_cgls_update_x(g, h->d_x, h->d_w, st, s))) return e;
-  if ((e = launch_cgls_update_r(g, h->d_u, h->d_t, st, red2, rw, s))) return e;
+  if ((e = launch_cgls_update(g, h->d_x, h->d_w, h->d_u, h->d_t, st, red1, rw + bc_parts(g), red2,
+                              rw, s)))
+    return e;
   if ((e = launch_rmv_chunks(g, c.prec, h->d_blocks, h->d_chunks, (int64_t)h->chunks.size(), c.A,
                              h->d_u, nullptr, h->d_part, st, s)))
     return e;
   if ((e = launch_rmv_finish(g, h->d_cstart, h->d_part, COL_STORE_SQ, h->d_v, st, red3, cw,
                              h->d_bc, h->d_u, nullptr, s)))
     return e;
-  if ((e = launch_cgls_step_b(st, red2, rw, red3, cw, s))) return e;
-  return launch_cgls_update_p(g, h->d_w, h->d_v, st, s);
+  return launch_cgls_update_p(g, h->d_w, h->d_v, st, red2, rw, red3, cw, s);
 }
 
 // u (LSQR) or r (CGLS) = rhs - A x0, the first bidiagonalisation step, x = x0 (LSQR without
@@ -193,10 +191,10 @@ hipError_t gram_mv(elmfb_problem h, const double* p, double* y, const SolveState
 
 // z = (R^T R)^{-1} r = R^{-1} R^{-T} r per block (block-Jacobi of the normal equations).
 hipError_t gcg_precond(elmfb_problem h, const double* r, double* z, const SolveState* st,
-                       hipStream_t s) {
+                       double* red, hipStream_t s) {
   hipError_t e = launch_bj_apply_t(h->geo, h->d_rinv, r, COL_STORE, h->d_gcg_tmp, st, nullptr, s);
   if (e != hipSuccess) return e;
-  return launch_bj_apply(h->geo, h->d_rinvT, h->d_gcg_tmp, nullptr, z, st, s);
+  return launch_bj_apply(h->geo, h->d_rinvT, h->d_gcg_tmp, nullptr, z, st, r, red, s);
 }
 
 // One CG step on G a = g.  a = d_x, r = d_v, p = d_w, q = d_vt, z = d_xt (c.bj) or r.
@@ -207,16 +205,14 @@ hipError_t gcg_iteration(elmfb_problem h, const KCtx& c, hipStream_t s) {
   const int cw = cols_wg(g);
   hipError_t e;
   if ((e = gram_mv(h, h->d_w, h->d_vt, st, red1, s))) return e;
-  if ((e = launch_gcg_alpha(st, red1, gmv_wg(g), s))) return e;
-  if ((e = launch_gcg_update(g, h->d_x, h->d_v, h->d_w, h->d_vt, st, red2, cw, s))) return e;
+  if ((e = launch_gcg_update(g, h->d_x, h->d_v, h->d_w, h->d_vt, st, red1, gmv_wg(g), red2, cw, s)))
+    return e;
   const double* z = h->d_v;
   if (c.bj) {
-    if ((e = gcg_precond(h, h->d_v, h->d_xt, st, s))) return e;
-    if ((e = launch_dot(h->d_v, h->d_xt, g.n_phi, st, red3, cw, s))) return e;
+    if ((e = gcg_precond(h, h->d_v, h->d_xt, st, red3, s))) return e;
     z = h->d_xt;
   }
-  if ((e = launch_gcg_beta(st, red2, cw, c.bj ? red3 : nullptr, cw, s))) return e;
-  return launch_gcg_pupdate(g, h->d_w, z, st, 0, s);
+  return launch_gcg_pupdate(g, h->d_w, z, st, red2, cw, c.bj ? red3 : nullptr, bj_wg(g), s);
 }
 
 // Start CG on G a = M^T rhs (rhs = c.rhs over the rows), from x0 or zero.
@@ -239,15 +235,15 @@ hipError_t gcg_start(elmfb_problem h, const KCtx& c, const double* x0, hipStream
   } else {
     if ((e = hipMemsetAsync(h->d_x, 0, (size_t)g.n_phi * 8, s))) return e;
   }
-  if ((e = launch_dot(h->d_v, h->d_v, g.n_phi, nullptr, red2, cw, s))) return e;
+  if ((e = launch_dot(h->d_v, h->d_v, g.n_phi, red2, cw, s))) return e;
   const double* z = h->d_v;
   if (c.bj) {
-    if ((e = gcg_precond(h, h->d_v, h->d_xt, nullptr, s))) return e;
-    if ((e = launch_dot(h->d_v, h->d_xt, g.n_phi, nullptr, red3, cw, s))) return e;
+    if ((e = gcg_precond(h, h->d_v, h->d_xt, nullptr, red3, s))) return e;
     z = h->d_xt;
   }
-  if ((e = launch_gcg_init(h->d_state, red1, cw, red2, cw, c.bj ? red3 : nullptr, cw, s))) return e;
-  return launch_gcg_pupdate(g, h->d_w, z, h->d_state, 1, s);
+  if ((e = launch_gcg_init(h->d_state, red1, cw, red2, cw, c.bj ? red3 : nullptr, bj_wg(g), s)))
+    return e;
+  return launch_copy(z, h->d_w, g.n_phi, s);
 }
 
 // Device tables of the stored Gram pairs for CG, rebuilt after every elmfb_gram call.
