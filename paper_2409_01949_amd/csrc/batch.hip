@@ -62,7 +62,7 @@ struct elmfb_batch_s {
   int32_t *d_flag = nullptr, *d_count = nullptr;
   double* d_rc = nullptr;      // block-Jacobi inverse factors R_b^{-1} (column-packed)
   double* d_Ahat = nullptr;    // preconditioned matrix M_b R_b^{-1} (FP64)
-  Tile* d_ftiles = nullptr;    // 64-point runs of the blocks (forming M R^{-1})
+  Tile* d_ftiles = nullptr;    // runs of the blocks' points (forming M R^{-1})
   std::vector<ColSlice> slices;    // one per subdomain block (the M^T U pass)
   std::vector<GramTask> tasks;     // one per subdomain block (the diagonal Gram blocks)
   ColSlice* d_slices = nullptr;
@@ -219,7 +219,6 @@ std::string plan_batch(elmfb_batch B, const elmfb_problem_desc* descs) {
       D.taby += tab_off;
       D.inst = i;
       B->blocks.push_back(D);
-      for (int p0 = 0; p0 < D.n; p0 += 64) B->ftiles.push_back(Tile{blk_off + (int32_t)b, p0});
       B->foff.push_back(f_off);
       B->goff.push_back(g_off);
       B->slices.push_back(ColSlice{blk_off + (int32_t)b, 0});
@@ -245,6 +244,9 @@ std::string plan_batch(elmfb_batch B, const elmfb_problem_desc* descs) {
     cov_off += (int32_t)hp.cov.size();
     if (row_off > ((int64_t)1 << 31) || col_off > ((int64_t)1 << 31)) return "batch too large";
   }
+  const int run = fold_run_points(B->kmax);
+  for (size_t b = 0; b < B->blocks.size(); ++b)
+    for (int p0 = 0; p0 < B->blocks[b].n; p0 += run) B->ftiles.push_back(Tile{(int32_t)b, p0});
   B->ftiles = xcd_grouped(B->ftiles);
   B->n_rows = row_off;
   B->n_phi = col_off;

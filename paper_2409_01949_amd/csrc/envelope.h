@@ -123,21 +123,29 @@ __device__ __forceinline__ float round_to_odd_f32(double v) {
   asm("" : "+v"(f));   // else the two conversions are merged into a 35-instruction FP64 to FP16
   return f;
 }
+template <int PREC>
+__device__ __forceinline__ uint16_t entry16(double v) {
+  if constexpr (PREC == ELMFB_BF16) {
+    const uint32_t sign = (uint32_t)(__double_as_longlong(v) >> 48) & 0x8000u;
+    // below the normals: RNE to multiples of the spacing 2^-133 by an addition
+    const double t = fabs(v) + 0x1.8p-81;
+    const uint32_t tiny = (uint32_t)__double_as_longlong(t);
+    const uint32_t u = __float_as_uint(round_to_odd_f32(fabs(v)));
+    const uint32_t r = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+    return (uint16_t)(sign | (fabs(v) < 0x1p-126 ? tiny : v == v ? r : 0x7fc0u));
+  } else {
+    // FP16's smallest spacing is 2^-24: what FP32 flushes on the way rounds to zero in any case
+    const _Float16 h = (_Float16)round_to_odd_f32(v);
+    return __builtin_bit_cast(uint16_t, h);
+  }
+}
 template <>
 __device__ __forceinline__ void store_entry<ELMFB_BF16>(void* A, int64_t i, double v) {
-  uint16_t r;
-  if (fabs(v) >= 0x1p-120) {     // FP32 normals; smaller values (and NaN) by the general rounding
-    const uint32_t u = __float_as_uint(round_to_odd_f32(v));
-    r = (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
-  } else {
-    r = f64_to_bf16_rne(v);
-  }
-  static_cast<uint16_t*>(A)[i] = r;
+  static_cast<uint16_t*>(A)[i] = entry16<ELMFB_BF16>(v);
 }
 template <>
 __device__ __forceinline__ void store_entry<ELMFB_FP16>(void* A, int64_t i, double v) {
-  // FP16's smallest spacing is 2^-24: what FP32 flushes on the way rounds to zero in any case
-  static_cast<_Float16*>(A)[i] = (_Float16)round_to_odd_f32(v);
+  static_cast<uint16_t*>(A)[i] = entry16<ELMFB_FP16>(v);
 }
 
 }  // namespace elmfb

@@ -694,8 +694,9 @@ elmfb_status elmfb_precondition(elmfb_problem h, double shift, int32_t* n_fallba
     const bool lo_ok = es_lo && h->d_Ahat_lo;
     if ((lo_ok || h->d_Ahat) && !h->d_ftiles) {
       std::vector<Tile> ft;
+      const int run = fold_run_points(g.K);
       for (size_t b = 0; b < h->blocks.size(); ++b)
-        for (int p0 = 0; p0 < h->blocks[b].n; p0 += 64) ft.push_back(Tile{(int32_t)b, p0});
+        for (int p0 = 0; p0 < h->blocks[b].n; p0 += run) ft.push_back(Tile{(int32_t)b, p0});
       HIP_OR_FAIL(h, dalloc_bytes(h, (void**)&h->d_ftiles, (int64_t)(ft.size() * sizeof(Tile)) + 16));
       if (!ft.empty())
         HIP_OR_FAIL(h, hipMemcpy(h->d_ftiles, ft.data(), ft.size() * sizeof(Tile),
