@@ -30,6 +30,7 @@ struct elmfb_mlp_s {
   double *d_part = nullptr, *d_loss = nullptr;
   float* d_ws = nullptr;                 // split-k partial products of the weight gradients
   float* d_colpart = nullptr;            // partial column sums of the bias gradients
+  int ldx = 0;                           // row stride of d_x: dims[0] rounded up to 8 (16-byte rows)
 };
 
 namespace {
@@ -71,7 +72,7 @@ MlpGemm layer_gemm(elmfb_mlp m, int l, const uint16_t* a_in, int batch) {
   g.N = m->dims[l + 1];
   g.K = m->dims[l];
   g.A = a_in;
-  g.sam = m->dims[l];
+  g.sam = l == 0 ? m->ldx : m->dims[l];
   g.sak = 1;
   g.B = m->d_pb + m->offW[l];
   g.sbk = 1;
@@ -82,7 +83,7 @@ MlpGemm layer_gemm(elmfb_mlp m, int l, const uint16_t* a_in, int batch) {
 }
 
 hipError_t run_forward(elmfb_mlp m, const float* x, int batch, float* y, hipStream_t s) {
-  hipError_t e = launch_mlp_to_bf16((int64_t)batch * m->dims[0], x, m->d_x, s);
+  hipError_t e = launch_mlp_rows_to_bf16(batch, m->dims[0], m->ldx, x, m->d_x, s);
   const uint16_t* a = m->d_x;
   for (int l = 0; l < m->L && e == hipSuccess; ++l) {
     MlpGemm g = layer_gemm(m, l, a, batch);
@@ -143,7 +144,8 @@ elmfb_status elmfb_mlp_create(int32_t n_layers, const int32_t* dims_host, int32_
   A(&m->d_m, o * 4);
   A(&m->d_v, o * 4);
   A(&m->d_pb, o * 2);
-  A(&m->d_x, B * m->dims[0] * 2);
+  m->ldx = (m->dims[0] + 7) / 8 * 8;
+  A(&m->d_x, B * m->ldx * 2);
   A(&m->d_y, B * m->dims[n_layers] * 4);
   A(&m->d_g1, B * m->max_dim * 2);
   A(&m->d_g2, B * m->max_dim * 2);
@@ -244,7 +246,7 @@ elmfb_status elmfb_mlp_train_step(elmfb_mlp m, const float* x_dev, const float* 
   for (int l = L - 1; l >= 0; --l) {
     const int n_in = m->dims[l], n_out = m->dims[l + 1];
     const uint16_t* a_in = l == 0 ? m->d_x : m->d_act[l];
-    // dW_l[n][k] = sum_m g[m][n] a_in[m][k]
+    // dW_l[n][k] = sum_m g[m][n] a_in[m][k], db_l[n] = sum_m g[m][n]
     MlpGemm gw{};
     gw.M = n_out;
     gw.N = n_in;
@@ -253,13 +255,14 @@ elmfb_status elmfb_mlp_train_step(elmfb_mlp m, const float* x_dev, const float* 
     gw.sam = 1;
     gw.sak = n_out;
     gw.B = a_in;
-    gw.sbk = n_in;
+    gw.sbk = l == 0 ? m->ldx : n_in;
     gw.sbn = 1;
     gw.epi = MLP_EPI_F32;
     gw.out_f32 = m->d_g + m->offW[l];
     gw.ldo = n_in;
+    gw.colsum = m->d_g + m->offb[l];
+    gw.colpart = m->d_colpart;
     MHIP(m, launch_mlp_gemm(gw, m->d_ws, s));
-    MHIP(m, launch_mlp_colsum(batch, n_out, g, m->d_colpart, m->d_g + m->offb[l], s));
     if (l > 0) {
       // g_prev[m][k] = (sum_n g[m][n] W[n][k]) (1 - a_in[m][k]^2)
       MlpGemm gb{};
