@@ -3,8 +3,8 @@
 //
 // The points are `rows` runs of `len` consecutive points of both operands (one run where the
 // shared box is a whole block).  A run is read in loads of 8 or 16 bytes (GramLoad) whatever its
-// alignment, the last one masked; a stage is 128 bytes of every feature row in LDS, the next stage's loads in registers meanwhile.  Row
-// stride 144 bytes: the 16 rows x 4 vectors of a fragment read fall on every bank equally.  A
+// alignment, the last one masked; a stage is 128 bytes of every feature row in LDS, the next
+// stage's loads in registers meanwhile.  Row stride 144 bytes: the 16 rows x 4 vectors of a fragment read fall on every bank equally.  A
 // lane's fragment is one 16-byte LDS read, which feeds one 16-bit MFMA or several of the FP32
 // and FP64 forms (k-slot lane/16 takes the lane's own points in turn: the same for X and Y).
 //
@@ -33,13 +33,16 @@ constexpr int kGrStride = kGrVecs + 1; // and of an LDS row: one of padding
 
 // One load: 16 bytes, but 8 where that measured faster.  The runs start at any entry, and a load off
 // its own size is split on the way: FP64 entries are loaded singly (all pairs of K = 96 8.7 against
-// 11.3 ms, K = 48 0.54 against 0.72); 16-bit entries by 4 on squares of 96 (1.9 against 2.2 ms; by
-// 8 on the others: K = 256 78 against 100 us, K = 48 122 against 134), FP32 entries by 4 (4.5
-// against 4.9 by 2 and 4.5 singly).
+// 11.3 ms, K = 48 0.54 against 0.72), FP32 entries by 4 (4.5 against 4.9 by 2 and 4.5 singly).
+// 16-bit entries on squares of 64 and 96 are loaded by 4 from the three dwords around them and cut
+// out: whole dwords are never split (K = 96 1.60 -> 1.54 ms, K = 48 120 -> 107 us, against 8-byte
+// and 16-byte loads where they lie); the other squares read 16 bytes (K = 256 73 against 80 us).
 typedef uint32_t gr_half __attribute__((ext_vector_type(2)));
 template <int PREC, int WT> struct GramLoad { typedef gr_vec t; };
 template <int WT> struct GramLoad<ELMFB_FP64, WT> { typedef double t; };
+template <> struct GramLoad<ELMFB_FP16, 2> { typedef gr_half t; };
 template <> struct GramLoad<ELMFB_FP16, 3> { typedef gr_half t; };
+template <> struct GramLoad<ELMFB_BF16, 2> { typedef gr_half t; };
 template <> struct GramLoad<ELMFB_BF16, 3> { typedef gr_half t; };
 
 // Points and operands of one product.
@@ -126,7 +129,12 @@ __device__ __forceinline__ void gram_product(const GramRun& R, gr_vec* lds, PUT 
       tJ[i] = 16 * J * kGrStride;
     }
   }
-  vec_t rx[NL], ry[NL];
+  // HALF: the dwords around each load, and the bits to its first point
+  constexpr bool HALF = ES == 2 && VB == 8;
+  struct wide_t { uint32_t d[3]; };
+  wide_t wx[HALF ? NL : 1], wy[HALF ? NL : 1];
+  uint32_t hx = 0, hy = 0;
+  vec_t rx[NL], ry[NL], mask{};
   int v = R.v0 + slot, run = v / nv, c = v - run * nv;
   auto fetch = [&]() {
     const int left = v < R.v1 ? R.len - c * VE : 0;            // points from this load on
@@ -140,9 +148,22 @@ __device__ __forceinline__ void gram_product(const GramRun& R, gr_vec* lds, PUT 
         if constexpr (VE > 1) m[d] = b == 4 ? ~0u : (1u << (8 * b)) - 1;
       }
     }
+    const char* px = R.x + ox;
+    const char* py = R.y + oy;
+    if constexpr (HALF) {
+      hx = 8 * ((uintptr_t)px & 2), hy = 8 * ((uintptr_t)py & 2);
+      px -= (uintptr_t)px & 2, py -= (uintptr_t)py & 2;
+      mask = m;
+    }
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       const int f = f0 + NR * i;
+      if constexpr (HALF) {
+        wx[i] = wy[i] = wide_t{};
+        if (left > 0 && f < R.nx) wx[i] = *reinterpret_cast<const wide_t*>(px + f * R.ldx);
+        if (!SAME && left > 0 && f < R.ny) wy[i] = *reinterpret_cast<const wide_t*>(py + f * R.ldy);
+        continue;
+      }
       rx[i] = ry[i] = vec_t{};
       if (left > 0 && f < R.nx) __builtin_memcpy(&rx[i], R.x + f * R.ldx + ox, VB);
       if (!SAME && left > 0 && f < R.ny) __builtin_memcpy(&ry[i], R.y + f * R.ldy + oy, VB);
@@ -166,6 +187,13 @@ __device__ __forceinline__ void gram_product(const GramRun& R, gr_vec* lds, PUT 
     __syncthreads();   // the previous stage's fragments are read
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
+      if constexpr (HALF) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          rx[i][e] = __builtin_amdgcn_alignbit(wx[i].d[e + 1], wx[i].d[e], hx) & mask[e];
+          ry[i][e] = __builtin_amdgcn_alignbit(wy[i].d[e + 1], wy[i].d[e], hy) & mask[e];
+        }
+      }
       Xs[(f0 + NR * i) * LS + slot] = rx[i];
       if (!SAME) Ys[(f0 + NR * i) * LS + slot] = ry[i];
     }

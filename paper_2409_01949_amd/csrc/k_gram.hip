@@ -17,12 +17,14 @@
 namespace elmfb {
 
 // Bound: FP64 by the matrix cores, 16-bit by the caches (a pair reads 2 K S entries for 2 K^2 S
-// flops); the host orders the chunks so that the pairs of one block follow each other on one XCD's
-// L2.  Staged before with one entry per load, every feature row by every group of output tiles,
-// chunks of 4,096 points whatever their number; computations, before -> now:
-//   3-level problem, 5,361 pairs of K = 96: FP64 9.6 -> 8.5 ms (47 TFLOP/s), FP32 5.9 -> 4.6,
-//     FP16 3.3 -> 1.9 ms (213 TFLOP/s); its diagonal blocks 1,522 -> 767, 964 -> 423, 557 -> 208 us
-//   11 blocks of K = 256: 1,957 -> 501, 1,642 -> 264, 1,167 -> 78 us
+// flops): the host orders the chunks so that the pairs of one second block, the finer of two
+// levels, follow each other on one XCD's L2 (by first block FP16 took 1.88 ms: 13 GB past the L2s
+// instead of 10.6; 8 or 40 groups an XCD instead of 16 1.62 and 1.61).  Staged before with one entry
+// per load, every feature row by every group of output tiles, chunks of 4,096 points whatever their
+// number; computations, before -> now:
+//   3-level problem, 5,361 pairs of K = 96: FP64 9.6 -> 8.5 ms (47 TFLOP/s), FP32 5.9 -> 4.5,
+//     FP16 3.3 -> 1.54 ms (260 TFLOP/s); its diagonal blocks 1,522 -> 750, 964 -> 422, 557 -> 202 us
+//   11 blocks of K = 256: 1,957 -> 480, 1,642 -> 257, 1,167 -> 73 us
 //   256 blocks of K = 16: 50 -> 20, 34 -> 14, 31 -> 11 us
 // (16 loads a row and stage instead of 8 take the registers of a wavefront a SIMD: FP64 8.7 -> 14 ms;
 // one contiguous range of chunks per XCD instead of dealt groups leaves the one with the coarse
@@ -101,8 +103,10 @@ __global__ void __launch_bounds__(256) k_gram_reduce(Geo g, const GramPair* __re
 
 template <int PREC>
 static int load_points(int K) {
-  const size_t b = gram_square(K) == 96 ? sizeof(typename GramLoad<PREC, 3>::t)
-                                        : sizeof(typename GramLoad<PREC, 1>::t);
+  const int side = gram_square(K);
+  const size_t b = side == 64   ? sizeof(typename GramLoad<PREC, 2>::t)
+                   : side == 96 ? sizeof(typename GramLoad<PREC, 3>::t)
+                                : sizeof(typename GramLoad<PREC, 1>::t);
   return (int)b / GramT<PREC>::es;
 }
 

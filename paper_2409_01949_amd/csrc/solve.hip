@@ -385,19 +385,33 @@ elmfb_status run_gram(elmfb_problem h, int prec, std::vector<GramPair>& pairs, v
     for (int64_t s0 = 0; s0 < nv; s0 += cv)
       chunks.push_back(GramChunk{(int32_t)p, (int32_t)(s0 / cv), (int32_t)s0});
   }
-  // Workgroups go to the 8 XCDs in turn: deal the chunks so that the pairs of one block i follow
-  // each other on one XCD, whose L2 then holds that block, in groups small enough to balance.
+  // Workgroups go to the 8 XCDs in turn: deal the chunks so that all pairs of one second block (the
+  // finer of two levels) and of its neighbours follow each other on one XCD, whose L2 then holds
+  // them, in groups small enough to balance (about 16 an XCD).
   {
-    constexpr int kXcd = 8, kGroup = 16;
+    constexpr int kXcd = 8;
+    std::vector<int32_t> at(g.n_blocks + 1, 0);
+    for (const GramChunk& c : chunks) ++at[pairs[c.pair].bj + 1];
+    for (int b = 0; b < g.n_blocks; ++b) at[b + 1] += at[b];
+    std::vector<GramChunk> by_j(chunks.size());
+    int64_t all = 0;
+    for (const GramChunk& c : chunks) {
+      by_j[at[pairs[c.pair].bj]++] = c;
+      all += std::min<int64_t>(cv, loads(pairs[c.pair]) - c.s0);
+    }
     std::vector<GramChunk> on[kXcd];
     int64_t load[kXcd] = {0};
-    for (size_t c = 0; c < chunks.size();) {
+    const int64_t group = all / (kXcd * 16);
+    for (size_t c = 0; c < by_j.size();) {
       const int x = (int)(std::min_element(load, load + kXcd) - load);
-      const int32_t bi = pairs[chunks[c].pair].bi;
-      for (int n = 0; c < chunks.size() && n < kGroup && pairs[chunks[c].pair].bi == bi; ++n, ++c) {
-        on[x].push_back(chunks[c]);
-        load[x] += std::min<int64_t>(cv, loads(pairs[chunks[c].pair]) - chunks[c].s0);
+      int64_t sum = 0;
+      int32_t bj = pairs[by_j[c].pair].bj;
+      for (; c < by_j.size() && (sum < group || pairs[by_j[c].pair].bj == bj) && sum <= 2 * group; ++c) {
+        bj = pairs[by_j[c].pair].bj;
+        on[x].push_back(by_j[c]);
+        sum += std::min<int64_t>(cv, loads(pairs[by_j[c].pair]) - by_j[c].s0);
       }
+      load[x] += sum;
     }
     size_t longest = 0;
     for (const auto& v : on) longest = std::max(longest, v.size());
