@@ -79,16 +79,23 @@ struct elmfb_problem_s {
   int64_t G_bytes = 0;
   void* d_gpart = nullptr;
   int64_t gpart_bytes = 0;
-  GramPair* d_gpairs = nullptr;
-  int64_t gpairs_cap = 0;
-  GramChunk* d_gchunks = nullptr;
-  int64_t gchunks_cap = 0;
-  int32_t* d_gmulti = nullptr;
-  int64_t gmulti_cap = 0;
-  std::vector<GramPair> gram_pairs_host;   // the pairs of the last elmfb_gram call
-  int64_t gram_gen = 0;                    // counts elmfb_gram calls
-  int64_t gram_nchunks = 0, gram_nmulti = 0;   // tables of the last Gram launch
-  int gram_chunk_vecs = 0;
+  // The launch tables of the diagonal blocks and of all pairs, of the precision last asked for
+  // (-1: none).  They depend on the geometry alone, so a new assembly keeps them.
+  struct GramPlan {
+    int prec = -1;
+    std::vector<GramPair> pairs;
+    GramPair* d_pairs = nullptr;
+    GramChunk* d_chunks = nullptr;
+    int32_t* d_multi = nullptr;
+    int64_t pairs_cap = 0, chunks_cap = 0, multi_cap = 0;
+    int64_t nchunks = 0, nmulti = 0, part_bytes = 0;
+    int chunk_vecs = 0;
+  };
+  GramPlan gplan[2];                       // by `which` of elmfb_gram
+  // counts changes of what a captured CG loop refers to: the kind, precision and buffer of the blocks
+  int64_t gram_gen = 0;
+  int gram_gen_prec = -1, gram_gen_which = -1;
+  void* gram_gen_G = nullptr;
 
   // CG on the Gram blocks: device copy of the stored pairs, per block-row tables of partials,
   // partials [2 n_pairs][K], and one extra coefficient vector for the preconditioner

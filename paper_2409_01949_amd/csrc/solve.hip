@@ -246,14 +246,15 @@ hipError_t gcg_start(elmfb_problem h, const KCtx& c, const double* x0, hipStream
   return launch_copy(z, h->d_w, g.n_phi, s);
 }
 
-// Device tables of the stored Gram pairs for CG, rebuilt after every elmfb_gram call.
+// Device tables of the stored Gram pairs for CG, rebuilt when their kind changes.
 elmfb_status gcg_prepare(elmfb_problem h) {
   if (h->gcg_gen == h->gram_gen) return ELMFB_OK;
   const Geo& g = h->geo;
+  const std::vector<GramPair>& pairs = h->gplan[h->gram_which].pairs;
   const int64_t np = h->gram_npairs;
   std::vector<std::vector<int32_t>> rows(g.n_blocks);
   for (int64_t p = 0; p < np; ++p) {
-    const GramPair& P = h->gram_pairs_host[p];
+    const GramPair& P = pairs[p];
     rows[P.bi].push_back((int32_t)(2 * p));
     if (P.bi != P.bj) rows[P.bj].push_back((int32_t)(2 * p + 1));
   }
@@ -277,7 +278,7 @@ elmfb_status gcg_prepare(elmfb_problem h) {
   HIP_OR_FAIL(h, dalloc(h, &h->d_gcg_part, 2 * np * g.K * 8));
   if (!h->d_gcg_tmp) HIP_OR_FAIL(h, dalloc(h, &h->d_gcg_tmp, g.n_phi * 8));
   if (np > 0)
-    HIP_OR_FAIL(h, hipMemcpy(h->d_gcg_pairs, h->gram_pairs_host.data(), np * sizeof(GramPair),
+    HIP_OR_FAIL(h, hipMemcpy(h->d_gcg_pairs, pairs.data(), np * sizeof(GramPair),
                              hipMemcpyHostToDevice));
   HIP_OR_FAIL(h, hipMemcpy(h->d_gcg_rowptr, row_ptr.data(), row_ptr.size() * 4,
                            hipMemcpyHostToDevice));
@@ -350,10 +351,21 @@ hipError_t check_solution(elmfb_problem h, const elmfb_solve_opts* o, const doub
                              nw, s);
 }
 
-// Plan the chunks of a set of Gram pairs, upload the tables, run the Gram kernel into G.
-elmfb_status run_gram(elmfb_problem h, int prec, std::vector<GramPair>& pairs, void* G,
-                      hipStream_t s) {
+// The launch tables of the diagonal blocks (which = 0) or of all pairs (1), on the device: made on
+// the first use and when the precision (the unit of chunks) changes.
+elmfb_status plan_gram(elmfb_problem h, int which, int prec, hipStream_t s) {
   const Geo& g = h->geo;
+  auto& plan = h->gplan[which];
+  if (plan.prec == prec) return ELMFB_OK;
+  plan.prec = -1;
+  std::vector<GramPair>& pairs = plan.pairs;
+  pairs.clear();
+  if (which == 1) {
+    pairs = h->pairs_all;
+  } else {
+    for (int64_t idx : h->diag_pair)
+      if (idx >= 0) pairs.push_back(h->pairs_all[idx]);
+  }
   const int64_t KK = (int64_t)g.K * g.K;
   std::vector<GramChunk> chunks;
   std::vector<int32_t> multi;
@@ -419,7 +431,6 @@ elmfb_status run_gram(elmfb_problem h, int prec, std::vector<GramPair>& pairs, v
     for (size_t i = 0; i < longest; ++i)
       for (const auto& v : on) chunks.push_back(i < v.size() ? v[i] : GramChunk{-1, 0, 0});
   }
-  const int64_t acc_es = prec == ELMFB_FP64 ? 8 : 4;
   auto grow = [&](void** buf, int64_t* cap, int64_t need) -> hipError_t {
     if (need <= *cap) return hipSuccess;
     dfree(h, *buf);
@@ -429,26 +440,47 @@ elmfb_status run_gram(elmfb_problem h, int prec, std::vector<GramPair>& pairs, v
     if (e == hipSuccess) *cap = need;
     return e;
   };
-  HIP_OR_FAIL(h, grow((void**)&h->d_gpairs, &h->gpairs_cap, (int64_t)pairs.size() * sizeof(GramPair)));
-  HIP_OR_FAIL(h, grow((void**)&h->d_gchunks, &h->gchunks_cap, (int64_t)chunks.size() * sizeof(GramChunk)));
-  HIP_OR_FAIL(h, grow((void**)&h->d_gmulti, &h->gmulti_cap, (int64_t)multi.size() * 4 + 4));
-  HIP_OR_FAIL(h, grow(&h->d_gpart, &h->gpart_bytes, p_off * KK * acc_es));
-  HIP_OR_FAIL(h, hipMemcpyAsync(h->d_gpairs, pairs.data(), pairs.size() * sizeof(GramPair),
+  HIP_OR_FAIL(h, grow((void**)&plan.d_pairs, &plan.pairs_cap, (int64_t)pairs.size() * sizeof(GramPair)));
+  HIP_OR_FAIL(h, grow((void**)&plan.d_chunks, &plan.chunks_cap, (int64_t)chunks.size() * sizeof(GramChunk)));
+  HIP_OR_FAIL(h, grow((void**)&plan.d_multi, &plan.multi_cap, (int64_t)multi.size() * 4 + 4));
+  HIP_OR_FAIL(h, hipMemcpyAsync(plan.d_pairs, pairs.data(), pairs.size() * sizeof(GramPair),
                                 hipMemcpyHostToDevice, s));
   if (!chunks.empty())
-    HIP_OR_FAIL(h, hipMemcpyAsync(h->d_gchunks, chunks.data(), chunks.size() * sizeof(GramChunk),
+    HIP_OR_FAIL(h, hipMemcpyAsync(plan.d_chunks, chunks.data(), chunks.size() * sizeof(GramChunk),
                                   hipMemcpyHostToDevice, s));
   if (!multi.empty())
-    HIP_OR_FAIL(h, hipMemcpyAsync(h->d_gmulti, multi.data(), multi.size() * 4,
+    HIP_OR_FAIL(h, hipMemcpyAsync(plan.d_multi, multi.data(), multi.size() * 4,
                                   hipMemcpyHostToDevice, s));
-  const void* A = prec == ELMFB_FP64 ? (const void*)h->d_A : h->d_A_lo;
-  HIP_OR_FAIL(h, launch_gram(g, prec, h->d_blocks, h->d_gpairs, h->d_gchunks,
-                             (int64_t)chunks.size(), cv, h->d_gmulti, (int64_t)multi.size(), A, G,
-                             h->d_gpart, s));
-  h->gram_chunk_vecs = cv;
-  h->gram_nchunks = (int64_t)chunks.size();
-  h->gram_nmulti = (int64_t)multi.size();
   // the host tables above must outlive the asynchronous copies
+  HIP_OR_FAIL(h, hipStreamSynchronize(s));
+  plan.chunk_vecs = cv;
+  plan.nchunks = (int64_t)chunks.size();
+  plan.nmulti = (int64_t)multi.size();
+  plan.part_bytes = p_off * KK * (prec == ELMFB_FP64 ? 8 : 4);
+  plan.prec = prec;
+  return ELMFB_OK;
+}
+
+hipError_t run_plan(elmfb_problem h, int which, void* G, hipStream_t s) {
+  const auto& plan = h->gplan[which];
+  const void* A = plan.prec == ELMFB_FP64 ? (const void*)h->d_A : h->d_A_lo;
+  return launch_gram(h->geo, plan.prec, h->d_blocks, plan.d_pairs, plan.d_chunks, plan.nchunks,
+                     plan.chunk_vecs, plan.d_multi, plan.nmulti, A, G, h->d_gpart, s);
+}
+
+// The Gram blocks of `which` into G, pair p at p K K; complete on return.
+elmfb_status run_gram(elmfb_problem h, int which, int prec, void* G, hipStream_t s) {
+  const elmfb_status st = plan_gram(h, which, prec, s);
+  if (st != ELMFB_OK) return st;
+  const int64_t need = h->gplan[which].part_bytes;
+  if (need > h->gpart_bytes) {
+    dfree(h, h->d_gpart);
+    h->d_gpart = nullptr;
+    h->gpart_bytes = 0;
+    HIP_OR_FAIL(h, dalloc_bytes(h, &h->d_gpart, need));
+    h->gpart_bytes = need;
+  }
+  HIP_OR_FAIL(h, run_plan(h, which, G, s));
   HIP_OR_FAIL(h, hipStreamSynchronize(s));
   return ELMFB_OK;
 }
@@ -533,15 +565,11 @@ elmfb_status elmfb_gram(elmfb_problem h, int32_t prec, int32_t which, void* stre
   if (which != 0 && which != 1) return fail(h, ELMFB_E_INVALID, "which must be 0 or 1");
   if (prec != ELMFB_FP64 && !(prec == h->lo_prec && h->d_A_lo))
     return fail(h, ELMFB_E_STATE, "no stored matrix copy in that precision");
-  std::vector<GramPair> pairs;
-  if (which == 1) {
-    pairs = h->pairs_all;
-  } else {
-    for (int64_t idx : h->diag_pair)
-      if (idx >= 0) pairs.push_back(h->pairs_all[idx]);
-  }
+  int64_t n_pairs = (int64_t)h->pairs_all.size();
+  if (which == 0)
+    n_pairs = std::count_if(h->diag_pair.begin(), h->diag_pair.end(), [](int64_t i) { return i >= 0; });
   const int64_t KK = (int64_t)h->geo.K * h->geo.K;
-  const int64_t need = (int64_t)pairs.size() * KK * (prec == ELMFB_FP64 ? 8 : 4);
+  const int64_t need = n_pairs * KK * (prec == ELMFB_FP64 ? 8 : 4);
   if (need > h->G_bytes) {
     dfree(h, h->d_G);
     h->d_G = nullptr;
@@ -553,10 +581,16 @@ elmfb_status elmfb_gram(elmfb_problem h, int32_t prec, int32_t which, void* stre
     h->G_bytes = need;
   }
   hipStream_t s = (hipStream_t)stream;
-  elmfb_status st = run_gram(h, prec, pairs, h->d_G, s);
+  elmfb_status st = run_gram(h, which, prec, h->d_G, s);
   if (st != ELMFB_OK) return st;
   h->gram_prec = prec;
   h->gram_which = which;
+  h->gram_npairs = n_pairs;
+  if (h->gram_gen_prec == prec && h->gram_gen_which == which && h->gram_gen_G == h->d_G)
+    return ELMFB_OK;   // captured CG loops read the new blocks where the old ones were
+  h->gram_gen_prec = prec;
+  h->gram_gen_which = which;
+  h->gram_gen_G = h->d_G;
   h->gram_gen += 1;
   // CG loops captured on the previous Gram blocks are keyed to the old generation and never
   // replayed again: release them once the stream has drained
@@ -573,8 +607,6 @@ elmfb_status elmfb_gram(elmfb_problem h, int32_t prec, int32_t which, void* stre
       ++it;
     }
   }
-  h->gram_npairs = (int64_t)pairs.size();
-  h->gram_pairs_host = pairs;
   return ELMFB_OK;
 }
 
@@ -586,19 +618,17 @@ elmfb_status elmfb_time_gram(elmfb_problem h, int32_t prec, int32_t which, int32
   const Geo& g = h->geo;
   if (flops_host) {
     double shared = 0.0;
-    for (const GramPair& P : h->gram_pairs_host) shared += (double)P.nx * P.ny;
+    for (const GramPair& P : h->gplan[h->gram_which].pairs) shared += (double)P.nx * P.ny;
     *flops_host = 2.0 * g.K * g.K * shared;
   }
   hipStream_t s = (hipStream_t)stream;
-  const void* A = prec == ELMFB_FP64 ? (const void*)h->d_A : h->d_A_lo;
   hipEvent_t e0, e1;
   HIP_OR_FAIL(h, hipEventCreate(&e0));
   HIP_OR_FAIL(h, hipEventCreate(&e1));
   // the tables of the call above are still on the device; relaunch the same computation
   hipError_t e = hipEventRecord(e0, s);
   for (int i = 0; i < reps && e == hipSuccess; ++i)
-    e = launch_gram(g, prec, h->d_blocks, h->d_gpairs, h->d_gchunks, h->gram_nchunks,
-                    h->gram_chunk_vecs, h->d_gmulti, h->gram_nmulti, A, h->d_G, h->d_gpart, s);
+    e = run_plan(h, which, h->d_G, s);
   if (e == hipSuccess) e = hipEventRecord(e1, s);
   if (e == hipSuccess) e = hipEventSynchronize(e1);
   float t = 0.f;
@@ -617,9 +647,10 @@ elmfb_status elmfb_copy_gram(elmfb_problem h, void* dst_dev, int64_t* pairs_host
   if (n_pairs_host) *n_pairs_host = h->gram_npairs;
   if (pairs_host)
     for (int64_t p = 0; p < h->gram_npairs; ++p) {
-      pairs_host[3 * p] = h->gram_pairs_host[p].bi;
-      pairs_host[3 * p + 1] = h->gram_pairs_host[p].bj;
-      pairs_host[3 * p + 2] = h->gram_pairs_host[p].g_off;
+      const GramPair& P = h->gplan[h->gram_which].pairs[p];
+      pairs_host[3 * p] = P.bi;
+      pairs_host[3 * p + 1] = P.bj;
+      pairs_host[3 * p + 2] = P.g_off;
     }
   if (dst_dev) {
     const int64_t KK = (int64_t)h->geo.K * h->geo.K;
@@ -648,28 +679,24 @@ elmfb_status elmfb_precondition(elmfb_problem h, double shift, int32_t* n_fallba
   double* gdiag = h->d_bj_work;
   double* rwork = h->d_bj_work + g.n_blocks * KK;
   // FP64 diagonal Gram blocks, one slot per block (empty blocks stay zero)
-  std::vector<GramPair> pairs;
   std::vector<int64_t> offs(g.n_blocks, 0);
   for (int b = 0; b < g.n_blocks; ++b) offs[b] = (int64_t)b * KK;
   HIP_OR_FAIL(h, hipMemsetAsync(gdiag, 0, (size_t)(g.n_blocks * KK * 8), s));
   std::vector<int> owner;
   for (int b = 0; b < g.n_blocks; ++b)
-    if (h->diag_pair[b] >= 0) {
-      pairs.push_back(h->pairs_all[h->diag_pair[b]]);
-      owner.push_back(b);
-    }
+    if (h->diag_pair[b] >= 0) owner.push_back(b);
   // run_gram places pair p at p*K*K; map through a compact buffer when blocks are empty
-  const bool dense_map = (int)pairs.size() == g.n_blocks;
+  const bool dense_map = (int)owner.size() == g.n_blocks;
   double* target = gdiag;
   if (!dense_map) {
     void* tmp = nullptr;
-    HIP_OR_FAIL(h, dalloc_bytes(h, &tmp, (int64_t)pairs.size() * KK * 8));
+    HIP_OR_FAIL(h, dalloc_bytes(h, &tmp, (int64_t)owner.size() * KK * 8));
     target = (double*)tmp;
   }
-  elmfb_status st = run_gram(h, ELMFB_FP64, pairs, target, s);
+  elmfb_status st = run_gram(h, 0, ELMFB_FP64, target, s);
   if (st != ELMFB_OK) return st;
   if (!dense_map) {
-    for (size_t p = 0; p < pairs.size(); ++p)
+    for (size_t p = 0; p < owner.size(); ++p)
       HIP_OR_FAIL(h, hipMemcpyAsync(gdiag + (int64_t)owner[p] * KK, target + (int64_t)p * KK,
                                     (size_t)KK * 8, hipMemcpyDeviceToDevice, s));
     HIP_OR_FAIL(h, hipStreamSynchronize(s));
