@@ -7,6 +7,8 @@
 // every subdomain's columns over its own support; LSQR then runs on M R^{-1} and the solution
 // is x = R^{-1} y.  Factors are computed once in FP64 (k_factor.hip) and R^{-1} is stored
 // explicitly together with its transpose, so both applications read memory contiguously.
+#include <algorithm>
+
 #include "device.h"
 #include "kernels.h"
 
@@ -20,6 +22,7 @@ namespace elmfb {
 // factor entries.
 constexpr int kBjRows = 32;
 constexpr int kBjSplit = 8;
+static_assert(kGcgBlockK == 128, "row groups of k_gcg_block");
 
 __device__ __forceinline__ int bj_tasks(const Geo& g) {
   return g.n_blocks * ((g.K + kBjRows - 1) / kBjRows);
@@ -144,6 +147,126 @@ __global__ void __launch_bounds__(256) k_bj_recover(Geo g, const double* __restr
     }
     __syncthreads();
   }
+}
+
+// The middle of a preconditioned CG step on the Gram blocks, one subdomain block per workgroup:
+// cg_a = gamma / (p . q) as in k_gcg_update, a += cg_a p ; r -= cg_a q, then, as r is the block's
+// own, z = R^{-1} (R^{-T} r) through LDS and the partials of r . r and r . z.  The sums of z run as in
+// k_bj_apply_t and k_bj_apply, whose launches this saves.  Bound by latency (launches, then the
+// chain of sums); KB: K rounded up to 64 or 128; up to 64 both factors' entries are loaded before
+// the step size is known, 8.5 -> 7.3 us.  A step in all, 6 -> 4 kernels: 81 blocks of K = 48 37 -> 32
+// us, 4 of K = 128 30.1 -> 29.4, 273 of K = 128 204 -> 193.
+template <int KB>
+__global__ void __launch_bounds__(256) k_gcg_block(
+    Geo g, double* __restrict__ a, double* __restrict__ r, const double* __restrict__ p,
+    const double* __restrict__ q, const double* __restrict__ rinv,
+    const double* __restrict__ rinvT, double* __restrict__ z, SolveState* st,
+    const double* __restrict__ red_pq, int n, double* __restrict__ red_rr,
+    double* __restrict__ red_rz) {
+  constexpr int G = KB / kBjRows, L = KB / kBjSplit;   // row groups, terms of a split
+  __shared__ double part[G][kBjSplit][kBjRows];
+  __shared__ double rs[KB], ts[KB];
+  __shared__ double sh[6];
+  const int K = g.K;
+  const int ro = threadIdx.x % kBjRows, sp = threadIdx.x / kBjRows;
+  double ri[G][L], rt[G][L];
+  // row o = kBjRows i + ro of R^{-T} (terms k <= o) or, upper, of R^{-1} (k >= o): term l of split sp
+  auto load = [&](double (&x)[G][L], const double* F, bool upper) {
+#pragma unroll
+    for (int i = 0; i < G; ++i)
+#pragma unroll
+      for (int l = 0; l < L; ++l) {
+        const int o = kBjRows * i + ro, k = upper ? o + sp + kBjSplit * l : sp + kBjSplit * l;
+        x[i][l] = o < K && (upper ? k < K : k <= o) ? F[(int64_t)k * K + o] : 0.0;
+      }
+  };
+  // its product with v: row kBjRows sp + ro in the threads with sp < G
+  auto apply = [&](const double (&x)[G][L], const double* v, bool upper) {
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+      double s = 0.0;
+#pragma unroll
+      for (int l = 0; l < L; ++l) {
+        const int o = kBjRows * i + ro, k = upper ? o + sp + kBjSplit * l : sp + kBjSplit * l;
+        if (o < K && (upper ? k < K : k <= o)) s += x[i][l] * v[k];
+      }
+      part[i][sp][ro] = s;
+    }
+    __syncthreads();
+    double t = 0.0;
+    if (sp < G) {
+#pragma unroll
+      for (int u = 0; u < kBjSplit; ++u) t += part[sp][u][ro];
+    }
+    return t;
+  };
+  int b = blockIdx.x;
+  load(ri, rinv + (int64_t)b * K * K, false);
+  if constexpr (KB <= 64) load(rt, rinvT + (int64_t)b * K * K, true);
+  bool live;
+  const double gamma = st->next_gamma;
+  const double pq = reduce_partials_live(red_pq, n, &st->done, sh, &live);
+  if (!live) return;
+  const bool ok = pq > 0.0;
+  const double al = ok ? gamma / pq : 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->cg_a = al;
+    st->gamma = gamma;
+    if (!ok) {
+      st->istop = 3;
+      st->done = 1;
+    }
+  }
+  if (!ok) return;
+  const int row = kBjRows * sp + ro;
+  double rr = 0.0, rz = 0.0;
+  while (true) {
+    const int64_t q0 = (int64_t)b * K;
+    if ((int)threadIdx.x < K) {
+      const int64_t t = q0 + threadIdx.x;
+      a[t] += al * p[t];
+      const double x = r[t] - al * q[t];
+      r[t] = x;
+      rs[threadIdx.x] = x;
+      rr += x * x;
+    }
+    __syncthreads();
+    const double y = apply(ri, rs, false);
+    if (sp < G && row < K) ts[row] = y;
+    if constexpr (KB > 64) load(rt, rinvT + q0 * K, true);
+    __syncthreads();
+    const double x = apply(rt, ts, true);
+    if (sp < G && row < K) {
+      z[q0 + row] = x;
+      rz += rs[row] * x;
+    }
+    b += gridDim.x;
+    if (b >= g.n_blocks) break;
+    load(ri, rinv + (int64_t)b * K * K, false);
+    if constexpr (KB <= 64) load(rt, rinvT + (int64_t)b * K * K, true);
+    __syncthreads();   // rs, ts and part are used again
+  }
+  rr = block_sum256(rr, sh);
+  rz = block_sum256(rz, sh);
+  if (threadIdx.x == 0) {
+    red_rr[blockIdx.x] = rr;
+    red_rz[blockIdx.x] = rz;
+  }
+}
+
+int gcg_block_wg(const Geo& g) { return std::min(g.n_blocks, kRedBlocks); }
+
+hipError_t launch_gcg_block(const Geo& g, double* a, double* r, const double* p, const double* q,
+                            const double* rinv, const double* rinvT, double* z, SolveState* st,
+                            const double* red_pq, int n_red, double* red_rr, double* red_rz,
+                            hipStream_t s) {
+  if (g.K > kGcgBlockK) return hipErrorInvalidValue;
+#define GCG_BLOCK(KB)                                                                            \
+  hipLaunchKernelGGL(k_gcg_block<KB>, dim3(gcg_block_wg(g)), dim3(256), 0, s, g, a, r, p, q, rinv, \
+                     rinvT, z, st, red_pq, n_red, red_rr, red_rz)
+  if (g.K <= 64) GCG_BLOCK(64); else GCG_BLOCK(128);
+#undef GCG_BLOCK
+  return hipGetLastError();
 }
 
 int bj_wg(const Geo& g) {

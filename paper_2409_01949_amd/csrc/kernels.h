@@ -141,6 +141,14 @@ hipError_t launch_gram(const Geo& g, int prec, const DevBlock* blocks, const Gra
 
 // ---- block-Jacobi preconditioner (k_precond.hip; the factors: k_factor.hip)
 int bj_wg(const Geo& g);
+// CG steps on blocks of up to this many features update and precondition in one kernel, a workgroup
+// per block; wider blocks are split over workgroups (two factors of K = 256 are 1 MB)
+constexpr int kGcgBlockK = 128;
+int gcg_block_wg(const Geo& g);   // its workgroups, each writing one partial of r . r and of r . z
+hipError_t launch_gcg_block(const Geo& g, double* a, double* r, const double* p, const double* q,
+                            const double* rinv, const double* rinvT, double* z, SolveState* st,
+                            const double* red_pq, int n_red, double* red_rr, double* red_rz,
+                            hipStream_t s);
 hipError_t launch_bj_factor(const Geo& g, const double* G, const int64_t* diag_off, double shift,
                             double* work, double* rinv, double* rinvT, int32_t* nfail,
                             hipStream_t s);

@@ -205,6 +205,12 @@ hipError_t gcg_iteration(elmfb_problem h, const KCtx& c, hipStream_t s) {
   const int cw = cols_wg(g);
   hipError_t e;
   if ((e = gram_mv(h, h->d_w, h->d_vt, st, red1, s))) return e;
+  if (c.bj && g.K <= kGcgBlockK) {
+    if ((e = launch_gcg_block(g, h->d_x, h->d_v, h->d_w, h->d_vt, h->d_rinv, h->d_rinvT, h->d_xt, st,
+                              red1, gmv_wg(g), red2, red3, s)))
+      return e;
+    return launch_gcg_pupdate(g, h->d_w, h->d_xt, st, red2, gcg_block_wg(g), red3, gcg_block_wg(g), s);
+  }
   if ((e = launch_gcg_update(g, h->d_x, h->d_v, h->d_w, h->d_vt, st, red1, gmv_wg(g), red2, cw, s)))
     return e;
   const double* z = h->d_v;
