@@ -739,6 +739,10 @@ def _kernel_label(name):
         targs[0] = _PREC_NAMES.get(targs[0], targs[0])
         if base == "k_rmv_chunks":
             targs = targs[:1]
+        elif base == "k_mv_blocks":
+            targs = targs[:2]      # not the rows loaded ahead
+    elif base == "k_gather_rows":
+        return base                # whatever rows and domain it is built for
     return f"{base}<{','.join(targs)}>"
 
 
