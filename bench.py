@@ -735,6 +735,8 @@ def _kernel_label(name):
     if not rest or "(" in base:
         return base
     targs = [t.strip() for t in rest.split(">")[0].split(",")]
+    if base == "k_bt_mvb_narrow":      # the narrow copies' form of the same pass
+        base = "k_bt_mvb"
     if base in ("k_mv_blocks", "k_bt_mvb", "k_bt_rmvb", "k_rmv_chunks"):
         targs[0] = _PREC_NAMES.get(targs[0], targs[0])
         if base == "k_rmv_chunks":

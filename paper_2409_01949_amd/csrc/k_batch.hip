@@ -233,6 +233,24 @@ __device__ __forceinline__ void bj_apply_lds(const double* __restrict__ rc, int 
 
 constexpr int kFacStage = 2048;   // doubles of a packed factor staged per round in A.v
 
+template <int PREC> struct StoreT;
+template <> struct StoreT<ELMFB_FP64> { typedef double t; };
+template <> struct StoreT<ELMFB_FP32> { typedef float t; };
+template <> struct StoreT<ELMFB_BF16> { typedef uint16_t t; };
+template <> struct StoreT<ELMFB_FP16> { typedef _Float16 t; };
+
+// Four consecutive entries of a narrow copy, and their values.
+template <int PREC> struct Quad;
+template <> struct Quad<ELMFB_FP32> { typedef float t __attribute__((ext_vector_type(4))); };
+template <> struct Quad<ELMFB_FP16> { typedef _Float16 t __attribute__((ext_vector_type(4))); };
+template <> struct Quad<ELMFB_BF16> { typedef uint16_t t __attribute__((ext_vector_type(4))); };
+
+template <int PREC>
+__device__ __forceinline__ double quad_f64(const typename Quad<PREC>::t& x, int i) {
+  if constexpr (PREC == ELMFB_BF16) return bf16_to_f64(x[i]);
+  else return (double)x[i];
+}
+
 // Partial rows of Y = A V: per block point, the block's contribution for every right-hand side,
 // tpart[(p_off + p) * R + rhs] (V scaled per pair by 1/alpha, or 0 once the pair is done).  The
 // waves take 64-point runs of the block in turn; each lane loads FA feature entries ahead of
@@ -241,6 +259,7 @@ constexpr int kFacStage = 2048;   // doubles of a packed factor staged per round
 // for the largest block).  Without runs a workgroup takes a whole block; with runs (patch blocks,
 // several hundred points over up to 512 columns) it takes one run of at most 256 points, so its
 // four waves get one 64-point group each (runs of a block are dealt to one XCD; blk = -1 pads).
+// FP64 entries; the narrow copies take k_bt_mvb_narrow.
 template <int PREC, int FA>
 __global__ void __launch_bounds__(256) k_bt_mvb(const DevBlock* __restrict__ blocks,
                                                 const Tile* __restrict__ runs,
@@ -286,6 +305,86 @@ __global__ void __launch_bounds__(256) k_bt_mvb(const DevBlock* __restrict__ blo
       }
       store_r(tpart + (B.p_off + p) * R, R, acc);
     }
+  }
+}
+
+typedef double bt_d4 __attribute__((ext_vector_type(4)));
+
+// The narrow copies' pass on v_mfma_f64_16x16x4_f64: 16 points x 4 features by 4 features x 8 right-
+// hand sides (the other 8 columns repeat them).  A wavefront takes 64 points, lane (li, lq) the
+// four points 4 li .. of feature 4 s + lq, which feed four products with one coefficient read from
+// LDS; on the vector units every entry takes four 16-byte reads of the coefficients, which bounds
+// them: 32 instances (2.4e8 FP32 entries, 2.4e6 points) 334 -> 299 us.  It needs its wavefronts: 4
+// per SIMD (110 registers) measured 346 us, 6 or 7 299.  Each lane loads FA / 4 steps of 4 features
+// ahead.  FP64 entries stay on the vector units (patches 172 against 183 us here).
+template <int PREC, int FA>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6)))
+    k_bt_mvb_narrow(const DevBlock* __restrict__ blocks, const Tile* __restrict__ runs,
+                    const void* __restrict__ A, const double* __restrict__ v, int R,
+                    const SolveState* __restrict__ st, double* __restrict__ tpart) {
+  typedef typename Quad<PREC>::t quad_t;
+  constexpr int AH = FA / 4;                       // steps of 4 features in flight
+  extern __shared__ double cs_dyn[];
+  double (*cs)[kMaxRhs] = reinterpret_cast<double (*)[kMaxRhs]>(cs_dyn);
+  const Tile run = runs ? runs[blockIdx.x] : Tile{(int32_t)blockIdx.x, 0};
+  if (run.blk < 0) return;
+  const DevBlock B = blocks[run.blk];
+  if (inst_all_done(st, B.inst, R)) return;
+  const int K = B.nk, nS = (K + 3) >> 2;
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 15, lq = lane >> 4;
+  const int n = runs ? min(B.n, run.p0 + 256) : B.n, ld = B.ld;
+  typedef typename StoreT<PREC>::t in_t;
+  const in_t* Ab = static_cast<const in_t*>(A) + B.a_off;
+  // rows start on 8-entry boundaries and ld is a multiple of 8: a lane's points lie wholly before
+  // ld or are past the block (then the row's first entries, whose sums are not stored)
+  auto fetch = [&](int p0, int s) {
+    const int k = 4 * s + lq, p = p0 + 4 * li;
+    return *reinterpret_cast<const quad_t*>(Ab + (int64_t)min(k, K - 1) * ld + (p < ld ? p : 0));
+  };
+  int p0 = run.p0 + wid * 64;
+  quad_t a[AH];
+  if (p0 < n) {
+#pragma unroll
+    for (int q = 0; q < AH; ++q) a[q] = fetch(p0, min(q, nS - 1));
+  }
+  for (int e = threadIdx.x; e < 4 * nS * kMaxRhs; e += 256) {
+    const int k = e >> 3, j = e & 7;
+    cs[k][j] = j < R && k < K
+                   ? v[(int64_t)(B.q0 + k) * R + j] * pair_scale(st, B.inst * R + j, true) : 0.0;
+  }
+  __syncthreads();
+  while (p0 < n) {
+    const int pn = p0 + 256;
+    bt_d4 acc[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] = bt_d4{0, 0, 0, 0};
+    for (int s0 = 0; s0 < nS; s0 += AH) {
+#pragma unroll
+      for (int q = 0; q < AH; ++q) {
+        const int s = s0 + q;
+        if (s < nS) {
+          const double c = cs[4 * s + lq][li & 7];
+          const bool in = 4 * s + lq < K;          // a last step's features past K
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? quad_f64<PREC>(a[q], t) : 0.0, c,
+                                                          acc[t], 0, 0, 0);
+          if (s + AH < nS) a[q] = fetch(p0, s + AH);
+          else if (pn < n) a[q] = fetch(pn, min(q, nS - 1));
+        }
+      }
+    }
+    // lane holds right-hand side li of the points 4 (lq + 4 i) + t
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int p = p0 + 4 * (lq + 4 * i) + t;
+        if (li < R && p < n) tpart[(B.p_off + p) * R + li] = acc[t][i];
+      }
+    p0 = pn;
   }
 }
 
@@ -400,12 +499,6 @@ __global__ void __launch_bounds__(256) k_bt_gather(const Geo* __restrict__ geos,
     if (threadIdx.x < kMaxRhs) red[(int64_t)blockIdx.x * kMaxRhs + threadIdx.x] = sum;
   }
 }
-
-template <int PREC> struct StoreT;
-template <> struct StoreT<ELMFB_FP64> { typedef double t; };
-template <> struct StoreT<ELMFB_FP32> { typedef float t; };
-template <> struct StoreT<ELMFB_BF16> { typedef uint16_t t; };
-template <> struct StoreT<ELMFB_FP16> { typedef _Float16 t; };
 
 template <int PREC>
 __device__ __forceinline__ double to_f64(typename StoreT<PREC>::t x) {
@@ -918,13 +1011,13 @@ static void mvb_fa(int prec, dim3 grid, size_t lds, const DevBlock* blocks, cons
                    hipStream_t s) {
   const dim3 blk(256);
   if (prec == ELMFB_FP32)
-    hipLaunchKernelGGL((k_bt_mvb<ELMFB_FP32, FA>), grid, blk, lds, s, blocks, runs, A, v, R, st,
+    hipLaunchKernelGGL((k_bt_mvb_narrow<ELMFB_FP32, FA>), grid, blk, lds, s, blocks, runs, A, v, R, st,
                        tpart);
   else if (prec == ELMFB_BF16)
-    hipLaunchKernelGGL((k_bt_mvb<ELMFB_BF16, FA>), grid, blk, lds, s, blocks, runs, A, v, R, st,
+    hipLaunchKernelGGL((k_bt_mvb_narrow<ELMFB_BF16, FA>), grid, blk, lds, s, blocks, runs, A, v, R, st,
                        tpart);
   else if (prec == ELMFB_FP16)
-    hipLaunchKernelGGL((k_bt_mvb<ELMFB_FP16, FA>), grid, blk, lds, s, blocks, runs, A, v, R, st,
+    hipLaunchKernelGGL((k_bt_mvb_narrow<ELMFB_FP16, FA>), grid, blk, lds, s, blocks, runs, A, v, R, st,
                        tpart);
   else
     hipLaunchKernelGGL((k_bt_mvb<ELMFB_FP64, FA>), grid, blk, lds, s, blocks, runs, A, v, R, st,
@@ -937,7 +1030,7 @@ hipError_t launch_bt_mvb(int prec, const DevBlock* blocks, const Tile* runs, int
   if (n_grid == 0) return hipSuccess;
   if (kmax < 1 || kmax > kPatchMaxK) return hipErrorInvalidValue;
   const dim3 grid((unsigned)n_grid);
-  const size_t lds = (size_t)kmax * kMaxRhs * sizeof(double);
+  const size_t lds = (size_t)(kmax + 3) / 4 * 4 * kMaxRhs * sizeof(double);
   if (fa == 4) mvb_fa<4>(prec, grid, lds, blocks, runs, A, v, R, st, tpart, s);
   else if (fa == 8) mvb_fa<8>(prec, grid, lds, blocks, runs, A, v, R, st, tpart, s);
   else if (fa == 16) mvb_fa<16>(prec, grid, lds, blocks, runs, A, v, R, st, tpart, s);
