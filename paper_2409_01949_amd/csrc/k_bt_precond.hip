@@ -98,10 +98,10 @@ __device__ __forceinline__ void fold_store(const DevBlock& B, int p, int I, int 
 // each wavefront then takes 16 NB points at a time with all their features, loading the rows of M
 // straight into the matrix cores' operand layout, one tile of 16 rows ahead.  Bound by HBM (M read,
 // FP64 and rounded copy written): the 3-level problem (K = 96, FP16 copy) 2,400 -> 1,090 us, 4.2
-// TB/s; 8,192 blocks of 64 to 128 columns (FP32 copy) 2,190 -> 1,700 us, 5.1 TB/s, against features
-// split over the wavefronts (K = 96 keeps half of them idle), both operands through one LDS buffer,
-// and the 16-bit rounding by integers.  J stays a loop: unrolled, the addresses of all tiles take
-// 400 registers.
+// TB/s; 8,192 blocks of 64 to 128 columns (FP32 copy; 250 points each, so that staging R^{-1} and
+// the first loads weigh) 2,190 -> 1,700 us, 2.8 TB/s, against features split over the wavefronts
+// (K = 96 keeps half of them idle), both operands through one LDS buffer, and the 16-bit rounding
+// by integers.  J stays a loop: unrolled, the addresses of all tiles take 400 registers.
 template <int LO, bool FULL, int NT>
 __global__ void __launch_bounds__(256)
     __attribute__((amdgpu_waves_per_eu(2))) k_bt_fold(const DevBlock* __restrict__ blocks,
@@ -198,8 +198,8 @@ __global__ void __launch_bounds__(256)
 // Up to 128 TPW columns (a patch's, or a single problem's wide block): 64 points per workgroup of 8
 // wavefronts, which own the feature tiles w, w + 8, ...; the contraction runs in stages of 16 rows
 // of M and of R^{-1} in two LDS buffers, the next stage's loads in flight during the products.  At
-// 512 columns the matrix cores are the bound (16 instances, patches of 2 x 2 subdomains of 64 to
-// 128 columns: 46 GFLOP with the zeros of the diagonal tiles): 3,110 -> 1,440 us.
+// 512 columns the stages' products and the latency of their loads are the bound (16 instances,
+// patches of 2 x 2 subdomains of 64 to 128 columns, about 30 GFLOP): 3,110 -> 1,440 us.
 template <int LO, bool FULL, int TPW>
 __global__ void __launch_bounds__(512) k_bt_fold_wide(const DevBlock* __restrict__ blocks,
                                                       const Tile* __restrict__ ftiles,
