@@ -84,9 +84,8 @@ struct elmfb_batch_s {
   std::vector<Tile> pftiles, pruns, pmvruns;
   std::vector<GramTask> ptasks;
   std::vector<int64_t> pfoff, pgoff;
-  std::vector<int64_t> pchunk_blk, pchunk_task;   // factor chunks: first block and first task
   int pkmax = 1;
-  int64_t pn_store = 0, pn_bp = 0, pn_fac = 0, pn_scratch = 0, pn_dense = 0;
+  int64_t pn_store = 0, pn_bp = 0, pn_fac = 0, pn_dense = 0;
   Geo* d_pgeos = nullptr;
   InstInfo* d_pinsts = nullptr;
   DevBlock* d_pblocks = nullptr;
@@ -271,10 +270,6 @@ int64_t factor_bytes(elmfb_batch B) {
   return b;
 }
 
-// Scratch for the Gram blocks and factors of the patches, per chunk of patches (two nk x nk
-// matrices per patch): the chunks are formed so that each needs at most this many doubles.
-constexpr int64_t kPatchScratch = (int64_t)1 << 28;   // 2 GiB of doubles per matrix set
-
 // Patch tables for P: per instance and level, patches of P consecutive subdomains along each
 // axis (the last along an axis keeps what is left), in x-major order; a patch block covers the
 // bounding box of its members' boxes (their union, as neighbouring supports overlap), holds their
@@ -285,8 +280,7 @@ std::string plan_patches(elmfb_batch B, int P) {
   B->pmoff.clear(); B->pperm.assign((size_t)B->n_phi, -1); B->pslices.clear();
   B->pftiles.clear(); B->pruns.clear(); B->pmvruns.clear(); B->ptasks.clear(); B->pfoff.clear();
   B->pgoff.clear();
-  B->pchunk_blk.clear(); B->pchunk_task.clear();
-  int64_t a_off = 0, p_off = 0, f_off = 0, dense = 0;
+  int64_t a_off = 0, p_off = 0, f_off = 0, g_off = 0, dense = 0;
   int kmax = 1;
   for (int i = 0; i < B->n; ++i) {
     const Geo& g = B->geos[i];
@@ -349,7 +343,9 @@ std::string plan_patches(elmfb_batch B, int P) {
           for (int i0 = 0; i0 < D.nk; i0 += kBatchMaxK)
             for (int j0 = i0; j0 < D.nk; j0 += kBatchMaxK) B->ptasks.push_back(GramTask{b, i0, j0});
           B->pfoff.push_back(f_off);
+          B->pgoff.push_back(g_off);
           f_off += (int64_t)D.nk * (D.nk + 1) / 2;
+          g_off += (int64_t)D.nk * D.nk;
           a_off += (int64_t)D.nk * D.ld;
           p_off += D.n;
           dense += (int64_t)D.nk * D.n;
@@ -363,7 +359,7 @@ std::string plan_patches(elmfb_batch B, int P) {
     B->pgeos.push_back(pg);
     B->pinsts.push_back(pi);
   }
-  // fold runs, dealt to the XCDs by block; factor chunks with their scratch offsets
+  // fold runs, dealt to the XCDs by block
   const int run = fold_run_points(kmax);
   std::vector<Tile> ft;
   for (size_t b = 0; b < B->pblocks.size(); ++b)
@@ -373,29 +369,64 @@ std::string plan_patches(elmfb_batch B, int P) {
   for (size_t b = 0; b < B->pblocks.size(); ++b)
     for (int p0 = 0; p0 < B->pblocks[b].n; p0 += 256) mr.push_back(Tile{(int32_t)b, p0});
   B->pmvruns = xcd_grouped(mr);
-  int64_t g_off = 0, scratch = 0;
-  size_t t = 0;
-  for (size_t b = 0; b < B->pblocks.size(); ++b) {
-    const int64_t sq = (int64_t)B->pblocks[b].nk * B->pblocks[b].nk;
-    if (b == 0 || g_off + sq > kPatchScratch) {
-      B->pchunk_blk.push_back((int64_t)b);
-      while (t < B->ptasks.size() && B->ptasks[t].blk < (int32_t)b) ++t;
-      B->pchunk_task.push_back((int64_t)t);
-      g_off = 0;
-    }
-    B->pgoff.push_back(g_off);
-    g_off += sq;
-    scratch = std::max(scratch, g_off);
-  }
-  B->pchunk_blk.push_back((int64_t)B->pblocks.size());
-  B->pchunk_task.push_back((int64_t)B->ptasks.size());
   B->pkmax = kmax;
   B->pn_store = a_off;
   B->pn_bp = p_off;
   B->pn_fac = f_off;
-  B->pn_scratch = scratch;
   B->pn_dense = dense;
   return "";
+}
+
+// Scratch for the Gram blocks and factors of a call, two nk x nk matrices a block, shared by chunks
+// of whole blocks: at most 2 GiB of doubles per matrix set (and what all the blocks take), less where
+// that does not fit beside what is held.
+constexpr int64_t kFactorScratch = (int64_t)1 << 28;
+
+struct FactorScratch {
+  elmfb_batch b;
+  double *G = nullptr, *W = nullptr;
+  int64_t cap = 0;             // doubles of each
+  explicit FactorScratch(elmfb_batch batch) : b(batch) {}
+  FactorScratch(const FactorScratch&) = delete;
+  ~FactorScratch() {
+    bfree(b, G);
+    bfree(b, W);
+  }
+  // all: the squares of all blocks; least: the largest block's
+  hipError_t take(int64_t all, int64_t least) {
+    for (cap = std::max(least, std::min(kFactorScratch, all));; cap = std::max(least, cap / 2)) {
+      hipError_t e = balloc(b, &G, cap * 8);
+      if (e == hipSuccess) e = balloc(b, &W, cap * 8);
+      if (e == hipSuccess) return e;
+      bfree(b, G);
+      G = nullptr;
+      if (cap == least) return e;
+      (void)hipGetLastError();   // else the next launch reports the failed allocation
+    }
+  }
+};
+
+// The Gram blocks and, into rc, the factors of the subdomain or patch blocks; goff: the offsets of
+// the blocks' squares one after the other, on the host and on the device.
+hipError_t factor_blocks(elmfb_batch B, const FactorScratch& S, const std::vector<DevBlock>& blocks,
+                         const std::vector<GramTask>& tasks, const std::vector<int64_t>& goff,
+                         const DevBlock* d_blocks, const GramTask* d_tasks, const int64_t* d_goff,
+                         const int64_t* d_foff, int kmax, const double* A, double shift, double* rc,
+                         hipStream_t s) {
+  const size_t nb = blocks.size();
+  hipError_t e = hipSuccess;
+  for (size_t b0 = 0, t0 = 0, b1, t1; b0 < nb && e == hipSuccess; b0 = b1, t0 = t1) {
+    for (b1 = b0; b1 < nb; ++b1)
+      if (goff[b1] + (int64_t)blocks[b1].nk * blocks[b1].nk - goff[b0] > S.cap) break;
+    for (t1 = t0; t1 < tasks.size() && tasks[t1].blk < (int32_t)b1;) ++t1;
+    double *G = S.G - goff[b0], *W = S.W - goff[b0];   // block b0's square starts the scratch
+    e = launch_bt_gram_diag(d_blocks, d_tasks + t0, (int64_t)(t1 - t0), kmax > kBatchMaxK, A, d_goff,
+                            G, s);
+    if (e == hipSuccess)
+      e = launch_bt_bj_factor(d_blocks, (int)b0, (int64_t)(b1 - b0), kmax, G, W, d_goff, d_foff,
+                              shift, rc, B->d_flag, s);
+  }
+  return e;
 }
 
 // The block structure a pass runs on: the subdomain blocks of the assembly, or the patch blocks
@@ -950,7 +981,6 @@ elmfb_status elmfb_batch_precondition_patches(elmfb_batch B, double shift, int32
   int32_t nfail = 0;
   hipError_t e = hipMemsetAsync(B->d_flag, 0, 4, s);
   if (patch == 1) {
-    const int64_t nb = (int64_t)B->blocks.size();
     if (!B->d_rc) {
       hipError_t e1 = balloc(B, &B->d_rc, B->n_fac * 8);
       hipError_t e2 = e1 == hipSuccess ? balloc(B, &B->d_Ahat, B->n_store * 8) : e1;
@@ -961,17 +991,13 @@ elmfb_status elmfb_batch_precondition_patches(elmfb_batch B, double shift, int32
         return bfail(B, ELMFB_E_NOMEM, std::string("factor storage: ") + hipGetErrorString(e2));
       }
     }
-    double *G = nullptr, *Wk = nullptr;
-    hipError_t e1 = balloc(B, &G, B->n_gsq * 8);
-    if (e1 == hipSuccess) e1 = balloc(B, &Wk, B->n_gsq * 8);
-    if (e1 != hipSuccess) bfree(B, G);
+    FactorScratch scratch(B);
+    const hipError_t e1 = scratch.take(B->n_gsq, (int64_t)B->kmax * B->kmax);
     if (e1 != hipSuccess)
       return bfail(B, ELMFB_E_NOMEM, std::string("Gram scratch: ") + hipGetErrorString(e1));
     if (e == hipSuccess)
-      e = launch_bt_gram_diag(B->d_blocks, B->d_tasks, nb, false, B->d_A, B->d_goff, G, s);
-    if (e == hipSuccess)
-      e = launch_bt_bj_factor(B->d_blocks, 0, nb, B->kmax, G, Wk, B->d_goff, B->d_foff, shift,
-                              B->d_rc, B->d_flag, s);
+      e = factor_blocks(B, scratch, B->blocks, B->tasks, B->goff, B->d_blocks, B->d_tasks, B->d_goff,
+                        B->d_foff, B->kmax, B->d_A, shift, B->d_rc, s);
     // M R^{-1} in FP64, and its rounded copy in place of the low-precision M
     if (e == hipSuccess)
       e = launch_bt_fold(B->lo_prec, false, B->kmax, B->d_blocks, B->d_ftiles,
@@ -979,8 +1005,6 @@ elmfb_status elmfb_batch_precondition_patches(elmfb_batch B, double shift, int32
                          B->d_A_lo, s);
     if (e == hipSuccess) e = hipMemcpyAsync(&nfail, B->d_flag, 4, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    bfree(B, G);
-    bfree(B, Wk);
     BHIP(B, e);
     B->lo_hat = B->lo_prec != ELMFB_FP64;
   } else {
@@ -1033,34 +1057,25 @@ elmfb_status elmfb_batch_precondition_patches(elmfb_batch B, double shift, int32
         return bfail(B, ELMFB_E_NOMEM, std::string("patch storage: ") + hipGetErrorString(e1));
       }
     }
-    double *G = nullptr, *Wk = nullptr;
-    hipError_t e1 = balloc(B, &G, B->pn_scratch * 8);
-    if (e1 == hipSuccess) e1 = balloc(B, &Wk, B->pn_scratch * 8);
-    if (e1 != hipSuccess) {
-      bfree(B, G);
+    FactorScratch scratch(B);
+    const DevBlock& last = B->pblocks.back();
+    const hipError_t e1 =
+        scratch.take(B->pgoff.back() + (int64_t)last.nk * last.nk, (int64_t)B->pkmax * B->pkmax);
+    if (e1 != hipSuccess)
       return bfail(B, ELMFB_E_NOMEM, std::string("patch Gram scratch: ") + hipGetErrorString(e1));
-    }
     // patches of M in FP64, then per chunk their Gram blocks and factors, then M R^{-1} in place
     if (e == hipSuccess)
       e = launch_bt_expand(B->d_geos, B->d_pblocks, B->d_pruns, (int64_t)B->pruns.size(),
                            B->d_blocks, B->d_pmem, B->d_pmoff, B->d_A, B->d_pAhat, s);
-    for (size_t c = 0; c + 1 < B->pchunk_blk.size() && e == hipSuccess; ++c) {
-      const int64_t b0 = B->pchunk_blk[c], b1 = B->pchunk_blk[c + 1];
-      const int64_t t0 = B->pchunk_task[c], t1 = B->pchunk_task[c + 1];
-      e = launch_bt_gram_diag(B->d_pblocks, B->d_ptasks + t0, t1 - t0, B->pkmax > kBatchMaxK,
-                              B->d_pAhat, B->d_pgoff, G, s);
-      if (e == hipSuccess)
-        e = launch_bt_bj_factor(B->d_pblocks, (int)b0, b1 - b0, B->pkmax, G, Wk, B->d_pgoff,
-                                B->d_pfoff, shift, B->d_prc, B->d_flag, s);
-    }
+    if (e == hipSuccess)
+      e = factor_blocks(B, scratch, B->pblocks, B->ptasks, B->pgoff, B->d_pblocks, B->d_ptasks,
+                        B->d_pgoff, B->d_pfoff, B->pkmax, B->d_pAhat, shift, B->d_prc, s);
     if (e == hipSuccess)
       e = launch_bt_fold(B->lo_prec, false, B->pkmax, B->d_pblocks, B->d_pftiles,
                          (int64_t)B->pftiles.size(), B->d_pAhat, B->d_prc, B->d_pfoff, B->d_pAhat,
                          B->d_plo, s);
     if (e == hipSuccess) e = hipMemcpyAsync(&nfail, B->d_flag, 4, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    bfree(B, G);
-    bfree(B, Wk);
     BHIP(B, e);
     B->lo_hat = false;   // the low-precision copy of M itself is untouched
   }
