@@ -382,11 +382,12 @@ elmfb_status plan_gram(elmfb_problem h, int which, int prec, hipStream_t s) {
     return (int64_t)rows * ((len + ve - 1) / ve);
   };
   // loads per chunk: about 8 workgroups a CU over the whole computation, from 512 points (a
-  // workgroup's fixed cost) to 8,192 (longer chunks only unbalance the last wave)
+  // workgroup's fixed cost) to 4,096: the longest sum an accumulator takes before a partial of it is
+  // written (8,192 equal products were up to twice as far off, in FP32 and in FP64)
   const int side = gram_square(g.K), squares = (g.K + side - 1) / side;
   int64_t total = 0;
   for (const GramPair& pr : pairs) total += loads(pr) * squares * squares;
-  const int64_t cv64 = std::min<int64_t>(8192 / ve, std::max<int64_t>(512 / ve, total / 2048));
+  const int64_t cv64 = std::min<int64_t>(4096 / ve, std::max<int64_t>(512 / ve, total / 2048));
   const int cv = (int)((cv64 + 31) / 32 * 32);
   int64_t p_off = 0;
   for (size_t p = 0; p < pairs.size(); ++p) {
