@@ -83,13 +83,14 @@ struct elmfb_problem_s {
   // (-1: none).  They depend on the geometry alone, so a new assembly keeps them.
   struct GramPlan {
     int prec = -1;
-    std::vector<GramPair> pairs;
-    GramPair* d_pairs = nullptr;
-    GramChunk* d_chunks = nullptr;
-    int32_t* d_multi = nullptr;
-    int64_t pairs_cap = 0, chunks_cap = 0, multi_cap = 0;
-    int64_t nchunks = 0, nmulti = 0, part_bytes = 0;
+    std::vector<char> tables;              // pairs, chunks and multi-chunk pairs as uploaded
+    char* d_tables = nullptr;
+    int64_t cap = 0;                       // bytes of d_tables
+    int64_t npairs = 0, nchunks = 0, nmulti = 0, part_bytes = 0;
     int chunk_vecs = 0;
+    int64_t chunks_at() const { return npairs * (int64_t)sizeof(GramPair); }
+    int64_t multi_at() const { return chunks_at() + nchunks * (int64_t)sizeof(GramChunk); }
+    GramPair* pairs() { return reinterpret_cast<GramPair*>(tables.data()); }
   };
   GramPlan gplan[2];                       // by `which` of elmfb_gram
   // counts changes of what a captured CG loop refers to: the kind, precision and buffer of the blocks

@@ -256,7 +256,7 @@ hipError_t gcg_start(elmfb_problem h, const KCtx& c, const double* x0, hipStream
 elmfb_status gcg_prepare(elmfb_problem h) {
   if (h->gcg_gen == h->gram_gen) return ELMFB_OK;
   const Geo& g = h->geo;
-  const std::vector<GramPair>& pairs = h->gplan[h->gram_which].pairs;
+  const GramPair* pairs = h->gplan[h->gram_which].pairs();
   const int64_t np = h->gram_npairs;
   std::vector<std::vector<int32_t>> rows(g.n_blocks);
   for (int64_t p = 0; p < np; ++p) {
@@ -284,7 +284,7 @@ elmfb_status gcg_prepare(elmfb_problem h) {
   HIP_OR_FAIL(h, dalloc(h, &h->d_gcg_part, 2 * np * g.K * 8));
   if (!h->d_gcg_tmp) HIP_OR_FAIL(h, dalloc(h, &h->d_gcg_tmp, g.n_phi * 8));
   if (np > 0)
-    HIP_OR_FAIL(h, hipMemcpy(h->d_gcg_pairs, pairs.data(), np * sizeof(GramPair),
+    HIP_OR_FAIL(h, hipMemcpy(h->d_gcg_pairs, pairs, np * sizeof(GramPair),
                              hipMemcpyHostToDevice));
   HIP_OR_FAIL(h, hipMemcpy(h->d_gcg_rowptr, row_ptr.data(), row_ptr.size() * 4,
                            hipMemcpyHostToDevice));
@@ -357,112 +357,116 @@ hipError_t check_solution(elmfb_problem h, const elmfb_solve_opts* o, const doub
                              nw, s);
 }
 
-// The launch tables of the diagonal blocks (which = 0) or of all pairs (1), on the device: made on
-// the first use and when the precision (the unit of chunks) changes.
+// Chunks from which their launch order matters: below, nearly all run at once (8 workgroups a CU).
+constexpr int64_t kDealChunks = 2048;
+
+// The launch tables of the diagonal blocks (which = 0) or of all pairs (1): made on the first use
+// and when the precision (the unit of chunks) changes, and uploaded on s in one copy.
 elmfb_status plan_gram(elmfb_problem h, int which, int prec, hipStream_t s) {
   const Geo& g = h->geo;
   auto& plan = h->gplan[which];
   if (plan.prec == prec) return ELMFB_OK;
   plan.prec = -1;
-  std::vector<GramPair>& pairs = plan.pairs;
-  pairs.clear();
-  if (which == 1) {
-    pairs = h->pairs_all;
-  } else {
-    for (int64_t idx : h->diag_pair)
-      if (idx >= 0) pairs.push_back(h->pairs_all[idx]);
-  }
   const int64_t KK = (int64_t)g.K * g.K;
-  std::vector<GramChunk> chunks;
-  std::vector<int32_t> multi;
   const int ve = gram_load_points(prec, g.K);   // points of a load, the unit of chunks
-  auto loads = [&](const GramPair& pr) {
+  std::vector<int64_t> at;                      // diagonal blocks: their place among all pairs
+  if (which == 0)
+    for (int64_t idx : h->diag_pair)
+      if (idx >= 0) at.push_back(idx);
+  const int64_t np = which == 1 ? (int64_t)h->pairs_all.size() : (int64_t)at.size();
+  auto source = [&](int64_t p) -> const GramPair& { return h->pairs_all[which == 1 ? p : at[p]]; };
+  std::vector<int64_t> nv(np);                  // loads of each pair
+  int64_t all = 0;
+  for (int64_t p = 0; p < np; ++p) {
+    const GramPair& pr = source(p);
     int rows, len;
     gram_runs(pr, h->blocks[pr.bi], h->blocks[pr.bj], &rows, &len);
-    return (int64_t)rows * ((len + ve - 1) / ve);
-  };
+    nv[p] = (int64_t)rows * ((len + ve - 1) / ve);
+    all += nv[p];
+  }
   // loads per chunk: about 8 workgroups a CU over the whole computation, from 512 points (a
   // workgroup's fixed cost) to 4,096: the longest sum an accumulator takes before a partial of it is
   // written (8,192 equal products were up to twice as far off, in FP32 and in FP64)
   const int side = gram_square(g.K), squares = (g.K + side - 1) / side;
-  int64_t total = 0;
-  for (const GramPair& pr : pairs) total += loads(pr) * squares * squares;
-  const int64_t cv64 = std::min<int64_t>(4096 / ve, std::max<int64_t>(512 / ve, total / 2048));
+  const int64_t cv64 =
+      std::min<int64_t>(4096 / ve, std::max<int64_t>(512 / ve, all * squares * squares / 2048));
   const int cv = (int)((cv64 + 31) / 32 * 32);
+  auto chunks_of = [&](int64_t p) { return (nv[p] + cv - 1) / cv; };
+  int64_t nch = 0, nmulti = 0;
+  for (int64_t p = 0; p < np; ++p) {
+    nch += chunks_of(p);
+    nmulti += chunks_of(p) > 1;
+  }
+  // Workgroups go to the 8 XCDs in turn: deal the chunks so that all pairs of one second block (the
+  // finer of two levels) and of its neighbours follow each other on one XCD, whose L2 then holds
+  // them, in groups small enough to balance (about 16 an XCD).  place[c]: chunk c of the pairs in
+  // `order` in the launch.
+  std::vector<int32_t> order, place;
+  int64_t nlist = nch;
+  if (nch > kDealChunks) {
+    constexpr int kXcd = 8;
+    std::vector<int32_t> start(g.n_blocks + 1, 0);
+    for (int64_t p = 0; p < np; ++p) ++start[source(p).bj + 1];
+    for (int b = 0; b < g.n_blocks; ++b) start[b + 1] += start[b];
+    order.resize(np);
+    for (int64_t p = 0; p < np; ++p) order[start[source(p).bj]++] = (int32_t)p;
+    place.reserve(nch);
+    int64_t load[kXcd] = {0}, group = all / (kXcd * 16), sum = 0;
+    int32_t on[kXcd] = {0};
+    int x = 0, bj = -1;
+    for (int32_t p : order) {
+      for (int64_t v = 0; v < nv[p]; v += cv) {
+        if (!((sum < group || source(p).bj == bj) && sum <= 2 * group)) {
+          load[x] += sum;
+          x = (int)(std::min_element(load, load + kXcd) - load);
+          sum = 0;
+        }
+        bj = source(p).bj;
+        place.push_back(kXcd * on[x]++ + x);
+        sum += std::min<int64_t>(cv, nv[p] - v);
+      }
+    }
+    nlist = (int64_t)kXcd * *std::max_element(on, on + kXcd);
+  }
+  plan.npairs = np;
+  plan.nchunks = nlist;
+  plan.nmulti = nmulti;
+  plan.tables.resize(plan.multi_at() + nmulti * 4);
+  GramPair* pairs = plan.pairs();
+  GramChunk* chunks = reinterpret_cast<GramChunk*>(plan.tables.data() + plan.chunks_at());
+  int32_t* multi = reinterpret_cast<int32_t*>(plan.tables.data() + plan.multi_at());
   int64_t p_off = 0;
-  for (size_t p = 0; p < pairs.size(); ++p) {
+  for (int64_t p = 0; p < np; ++p) {
     GramPair& pr = pairs[p];
-    const int64_t nv = loads(pr);
-    pr.g_off = (int64_t)p * KK;
-    pr.nchunks = (int32_t)((nv + cv - 1) / cv);
+    pr = source(p);
+    pr.g_off = p * KK;
+    pr.nchunks = (int32_t)chunks_of(p);
     pr.p_off = 0;
     if (pr.nchunks > 1) {
       pr.p_off = p_off;
       p_off += pr.nchunks;
-      multi.push_back((int32_t)p);
+      *multi++ = (int32_t)p;
     }
-    for (int64_t s0 = 0; s0 < nv; s0 += cv)
-      chunks.push_back(GramChunk{(int32_t)p, (int32_t)(s0 / cv), (int32_t)s0});
   }
-  // Workgroups go to the 8 XCDs in turn: deal the chunks so that all pairs of one second block (the
-  // finer of two levels) and of its neighbours follow each other on one XCD, whose L2 then holds
-  // them, in groups small enough to balance (about 16 an XCD).
-  {
-    constexpr int kXcd = 8;
-    std::vector<int32_t> at(g.n_blocks + 1, 0);
-    for (const GramChunk& c : chunks) ++at[pairs[c.pair].bj + 1];
-    for (int b = 0; b < g.n_blocks; ++b) at[b + 1] += at[b];
-    std::vector<GramChunk> by_j(chunks.size());
-    int64_t all = 0;
-    for (const GramChunk& c : chunks) {
-      by_j[at[pairs[c.pair].bj]++] = c;
-      all += std::min<int64_t>(cv, loads(pairs[c.pair]) - c.s0);
-    }
-    std::vector<GramChunk> on[kXcd];
-    int64_t load[kXcd] = {0};
-    const int64_t group = all / (kXcd * 16);
-    for (size_t c = 0; c < by_j.size();) {
-      const int x = (int)(std::min_element(load, load + kXcd) - load);
-      int64_t sum = 0;
-      int32_t bj = pairs[by_j[c].pair].bj;
-      for (; c < by_j.size() && (sum < group || pairs[by_j[c].pair].bj == bj) && sum <= 2 * group; ++c) {
-        bj = pairs[by_j[c].pair].bj;
-        on[x].push_back(by_j[c]);
-        sum += std::min<int64_t>(cv, loads(pairs[by_j[c].pair]) - by_j[c].s0);
-      }
-      load[x] += sum;
-    }
-    size_t longest = 0;
-    for (const auto& v : on) longest = std::max(longest, v.size());
-    chunks.clear();
-    for (size_t i = 0; i < longest; ++i)
-      for (const auto& v : on) chunks.push_back(i < v.size() ? v[i] : GramChunk{-1, 0, 0});
+  if (!place.empty()) std::fill_n(chunks, nlist, GramChunk{-1, 0, 0});
+  int64_t c = 0;
+  for (int64_t i = 0; i < np; ++i) {
+    const int32_t p = place.empty() ? (int32_t)i : order[i];
+    for (int32_t k = 0; k < pairs[p].nchunks; ++k, ++c)
+      chunks[place.empty() ? c : place[c]] = GramChunk{p, k, k * cv};
   }
-  auto grow = [&](void** buf, int64_t* cap, int64_t need) -> hipError_t {
-    if (need <= *cap) return hipSuccess;
-    dfree(h, *buf);
-    *buf = nullptr;
-    *cap = 0;
-    hipError_t e = dalloc_bytes(h, buf, need);
-    if (e == hipSuccess) *cap = need;
-    return e;
-  };
-  HIP_OR_FAIL(h, grow((void**)&plan.d_pairs, &plan.pairs_cap, (int64_t)pairs.size() * sizeof(GramPair)));
-  HIP_OR_FAIL(h, grow((void**)&plan.d_chunks, &plan.chunks_cap, (int64_t)chunks.size() * sizeof(GramChunk)));
-  HIP_OR_FAIL(h, grow((void**)&plan.d_multi, &plan.multi_cap, (int64_t)multi.size() * 4 + 4));
-  HIP_OR_FAIL(h, hipMemcpyAsync(plan.d_pairs, pairs.data(), pairs.size() * sizeof(GramPair),
-                                hipMemcpyHostToDevice, s));
-  if (!chunks.empty())
-    HIP_OR_FAIL(h, hipMemcpyAsync(plan.d_chunks, chunks.data(), chunks.size() * sizeof(GramChunk),
+  const int64_t bytes = (int64_t)plan.tables.size();
+  if (bytes > plan.cap) {
+    dfree(h, plan.d_tables);
+    plan.d_tables = nullptr;
+    plan.cap = 0;
+    HIP_OR_FAIL(h, dalloc(h, &plan.d_tables, bytes));
+    plan.cap = bytes;
+  }
+  if (bytes > 0)
+    HIP_OR_FAIL(h, hipMemcpyAsync(plan.d_tables, plan.tables.data(), (size_t)bytes,
                                   hipMemcpyHostToDevice, s));
-  if (!multi.empty())
-    HIP_OR_FAIL(h, hipMemcpyAsync(plan.d_multi, multi.data(), multi.size() * 4,
-                                  hipMemcpyHostToDevice, s));
-  // the host tables above must outlive the asynchronous copies
-  HIP_OR_FAIL(h, hipStreamSynchronize(s));
   plan.chunk_vecs = cv;
-  plan.nchunks = (int64_t)chunks.size();
-  plan.nmulti = (int64_t)multi.size();
   plan.part_bytes = p_off * KK * (prec == ELMFB_FP64 ? 8 : 4);
   plan.prec = prec;
   return ELMFB_OK;
@@ -471,8 +475,12 @@ elmfb_status plan_gram(elmfb_problem h, int which, int prec, hipStream_t s) {
 hipError_t run_plan(elmfb_problem h, int which, void* G, hipStream_t s) {
   const auto& plan = h->gplan[which];
   const void* A = plan.prec == ELMFB_FP64 ? (const void*)h->d_A : h->d_A_lo;
-  return launch_gram(h->geo, plan.prec, h->d_blocks, plan.d_pairs, plan.d_chunks, plan.nchunks,
-                     plan.chunk_vecs, plan.d_multi, plan.nmulti, A, G, h->d_gpart, s);
+  return launch_gram(h->geo, plan.prec, h->d_blocks,
+                     reinterpret_cast<const GramPair*>(plan.d_tables),
+                     reinterpret_cast<const GramChunk*>(plan.d_tables + plan.chunks_at()),
+                     plan.nchunks, plan.chunk_vecs,
+                     reinterpret_cast<const int32_t*>(plan.d_tables + plan.multi_at()), plan.nmulti,
+                     A, G, h->d_gpart, s);
 }
 
 // The Gram blocks of `which` into G, pair p at p K K; complete on return.
@@ -480,15 +488,20 @@ elmfb_status run_gram(elmfb_problem h, int which, int prec, void* G, hipStream_t
   const elmfb_status st = plan_gram(h, which, prec, s);
   if (st != ELMFB_OK) return st;
   const int64_t need = h->gplan[which].part_bytes;
+  hipError_t e = hipSuccess;
   if (need > h->gpart_bytes) {
     dfree(h, h->d_gpart);
     h->d_gpart = nullptr;
     h->gpart_bytes = 0;
-    HIP_OR_FAIL(h, dalloc_bytes(h, &h->d_gpart, need));
-    h->gpart_bytes = need;
+    e = dalloc_bytes(h, &h->d_gpart, need);
+    if (e == hipSuccess) h->gpart_bytes = need;
   }
-  HIP_OR_FAIL(h, run_plan(h, which, G, s));
-  HIP_OR_FAIL(h, hipStreamSynchronize(s));
+  if (e == hipSuccess) e = run_plan(h, which, G, s);
+  // also after an error: the plan's tables on the host must outlive their copy
+  const hipError_t es = hipStreamSynchronize(s);
+  if (es != hipSuccess) h->gplan[which].prec = -1;
+  HIP_OR_FAIL(h, e);
+  HIP_OR_FAIL(h, es);
   return ELMFB_OK;
 }
 
@@ -625,7 +638,8 @@ elmfb_status elmfb_time_gram(elmfb_problem h, int32_t prec, int32_t which, int32
   const Geo& g = h->geo;
   if (flops_host) {
     double shared = 0.0;
-    for (const GramPair& P : h->gplan[h->gram_which].pairs) shared += (double)P.nx * P.ny;
+    const GramPair* pairs = h->gplan[which].pairs();
+    for (int64_t p = 0; p < h->gram_npairs; ++p) shared += (double)pairs[p].nx * pairs[p].ny;
     *flops_host = 2.0 * g.K * g.K * shared;
   }
   hipStream_t s = (hipStream_t)stream;
@@ -654,7 +668,7 @@ elmfb_status elmfb_copy_gram(elmfb_problem h, void* dst_dev, int64_t* pairs_host
   if (n_pairs_host) *n_pairs_host = h->gram_npairs;
   if (pairs_host)
     for (int64_t p = 0; p < h->gram_npairs; ++p) {
-      const GramPair& P = h->gplan[h->gram_which].pairs[p];
+      const GramPair& P = h->gplan[h->gram_which].pairs()[p];
       pairs_host[3 * p] = P.bi;
       pairs_host[3 * p + 1] = P.bj;
       pairs_host[3 * p + 2] = P.g_off;
