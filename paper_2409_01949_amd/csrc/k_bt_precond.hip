@@ -17,7 +17,9 @@ typedef double d4_t __attribute__((ext_vector_type(4)));
 // One square of G_b (a GramTask: rows i0.., columns j0.., at most 128 each; on the diagonal the
 // tiles I <= J), FP64, over all points of the block (gram_product).  8,192 blocks of K = 64 to 128
 // 1,944 -> 955 us, patches of up to 512 columns (16 instances) 1,741 -> 958 us, against tiles dealt
-// with a search per product and stages of 32 points without prefetch.
+// with a search per product and stages of 32 points without prefetch.  WT: squares of 32 WT columns
+// for the batch's widest block (the staging of 128 rows was the time of narrow blocks).
+template <int WT>
 __global__ void __launch_bounds__(256) k_bt_gram_diag(const DevBlock* __restrict__ blocks,
                                                       const GramTask* __restrict__ tasks,
                                                       const double* __restrict__ A,
@@ -39,8 +41,8 @@ __global__ void __launch_bounds__(256) k_bt_gram_diag(const DevBlock* __restrict
   R.v1 = B.n;
   double* out = G + goff[T.blk] + (int64_t)T.i0 * K + T.j0;
   auto put = [&](int r, int c, double v) { out[r * K + c] = v; };
-  if (T.i0 == T.j0) gram_product<ELMFB_FP64, 4, GRAM_UPPER>(R, gd_lds, put);
-  else gram_product<ELMFB_FP64, 4, GRAM_SQUARE>(R, gd_lds, put);
+  if (T.i0 == T.j0) gram_product<ELMFB_FP64, WT, GRAM_UPPER>(R, gd_lds, put);
+  else if constexpr (WT == 4) gram_product<ELMFB_FP64, 4, GRAM_SQUARE>(R, gd_lds, put);
 }
 
 // Fold the preconditioner into the matrix: Mhat_b = M_b R_b^{-1}, i.e. in the feature-major
@@ -372,17 +374,17 @@ __global__ void __launch_bounds__(256) k_bt_expand(const Geo* __restrict__ geos,
 }
 
 hipError_t launch_bt_gram_diag(const DevBlock* blocks, const GramTask* tasks, int64_t n_tasks,
-                               bool two_panels, const double* A, const int64_t* goff, double* G,
+                               int kmax, const double* A, const int64_t* goff, double* G,
                                hipStream_t s) {
   if (n_tasks == 0) return hipSuccess;
-  const size_t lds = (size_t)(two_panels ? 2 : 1) * kBatchMaxK * kGrStride * sizeof(gr_vec);
-  if (two_panels) {   // 68 KB
-    const hipError_t e = hipFuncSetAttribute((const void*)k_bt_gram_diag,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(k_bt_gram_diag, dim3((unsigned)n_tasks), dim3(256), lds, s, blocks, tasks, A,
-                     goff, G);
+  const int wt = kmax > 64 ? 4 : kmax > 32 ? 2 : 1;
+  // above 128 columns also squares off the diagonal, which stage two operands
+  const size_t lds = (size_t)(kmax > kBatchMaxK ? 2 : 1) * 32 * wt * kGrStride * sizeof(gr_vec);
+#define GRAM_DIAG(W)                                                                              \
+  hipLaunchKernelGGL(k_bt_gram_diag<W>, dim3((unsigned)n_tasks), dim3(256), lds, s, blocks, tasks, \
+                     A, goff, G)
+  if (wt == 4) GRAM_DIAG(4); else if (wt == 2) GRAM_DIAG(2); else GRAM_DIAG(1);
+#undef GRAM_DIAG
   return hipGetLastError();
 }
 

@@ -45,33 +45,37 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
                           __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
 
-// The 16 x 16 diagonal block in Pn[0..16)[c0..c0 + 16) plus lam I by one wavefront (columns from nb
-// on are the identity's): its Cholesky factor to D
-// (zero below the diagonal) and the reciprocals of its diagonal to dinv; prow: 16 doubles of LDS
-// for the pivot row.  False on a pivot <= 0.
-__device__ __forceinline__ bool factor_diag(const double* Pn, const int pw, int c0, int nb,
-                                            double lam, double* D, double* dinv, double* prow) {
-  const int li = threadIdx.x & 15;
-  double col[16];
+// The N x N diagonal block (N <= 32) in Pn[0..N)[c0..c0 + N) plus lam I by one wavefront: its Cholesky
+// factor to D (zero below the diagonal) and the reciprocals of its diagonal to dinv; prow: LN doubles
+// of LDS for the pivot row.  Rows and columns from nb on become the identity's first.  False on a
+// pivot <= 0.
+template <int N>
+__device__ __forceinline__ bool factor_diag(double* Pn, const int pw, int c0, int nb, double lam,
+                                            double* D, double* dinv, double* prow) {
+  constexpr int LN = N > 16 ? 32 : 16, LD = LN + 1;   // lanes to a row, row stride of D
+  const int li = threadIdx.x % LN;
+  for (int i = (threadIdx.x & 63) / LN; nb < N && i < N; i += 64 / LN)
+    if (i >= nb || li >= nb) Pn[i * pw + c0 + li] = i == li ? 1.0 : 0.0;
+  __builtin_amdgcn_wave_barrier();       // LDS is in order within a wavefront
+  double col[N];
 #pragma unroll
-  for (int i = 0; i < 16; ++i)
-    col[i] = li < nb ? Pn[i * pw + c0 + li] + (i == li ? lam : 0.0) : (i == li ? 1.0 : 0.0);
+  for (int i = 0; i < N; ++i) col[i] = Pn[i * pw + c0 + li] + (i == li ? lam : 0.0);
   bool ok = true;
 #pragma unroll
-  for (int k = 0; k < 16; ++k) {
+  for (int k = 0; k < N; ++k) {
     const double d = lane_value(col[k], k);
     ok = ok && d > 0.0;
     const double rk = sqrt(d > 0.0 ? d : 1.0);
     col[k] = li == k ? rk : col[k] / rk;
     if (li == k) dinv[k] = 1.0 / rk;
-    prow[li] = col[k];                   // four lanes write the same value; in order within a wave
+    prow[li] = col[k];                   // the lanes of a column write the same value; in order within a wave
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int i = k + 1; i < 16; ++i) col[i] -= prow[i] * col[k];
+    for (int i = k + 1; i < N; ++i) col[i] -= prow[i] * col[k];
     __builtin_amdgcn_wave_barrier();
   }
 #pragma unroll
-  for (int i = 0; i < 16; ++i) D[i * kFacDiag + li] = li >= i ? col[i] : 0.0;
+  for (int i = 0; i < N; ++i) D[i * LD + li] = li >= i ? col[i] : 0.0;
   return ok;
 }
 
@@ -195,7 +199,7 @@ k_bj_factor(const DevBlock* __restrict__ blocks,
           __syncthreads();
         }
         if (wid == 0) {
-          const bool ok = factor_diag(Pn, pw, 16 * r, K - i0, lam, D, dinv, prow);
+          const bool ok = factor_diag<16>(Pn, pw, 16 * r, K - i0, lam, D, dinv, prow);
           if (lane == 0) bad_s = !ok;
         }
         __syncthreads();
@@ -378,12 +382,66 @@ k_bj_factor(const DevBlock* __restrict__ blocks,
   }
 }
 
+// K <= N <= 32: one wavefront a block, the inverse a column per lane; arguments as above, without W.
+// A chain of K pivots without the panels' barriers: 60 batched blocks of K = 4 / 7 / 16 / 20 take a
+// precondition call of 41.7 / 47.6 / 47.7 / 60.0 us, 60.9 / 60.4 / 60.8 / 65.6 by panels.
+template <bool FULL, int N>
+__global__ void __launch_bounds__(64) k_bj_factor_tile(const DevBlock* __restrict__ blocks, int blk0,
+                                                       int Kall, const double* __restrict__ G,
+                                                       double* __restrict__ X,
+                                                       const int64_t* __restrict__ goff,
+                                                       const int64_t* __restrict__ foff, double shift,
+                                                       double* __restrict__ rc,
+                                                       double* __restrict__ rinvT,
+                                                       int32_t* __restrict__ nfail) {
+  constexpr int LN = N > 16 ? 32 : 16, LD = LN + 1;
+  __shared__ double S[N * LD], D[N * LD], dinv[LN], prow[LN];
+  const int b = blk0 + (int)blockIdx.x, K = FULL ? Kall : blocks[b].nk;
+  const int li = threadIdx.x % LN;
+  const double* Gb = G + goff[b];
+  for (int i = threadIdx.x / LN; i < N; i += 64 / LN)
+    S[i * LD + li] = i < K && li < K ? Gb[min(i, li) * K + max(i, li)] : 0.0;
+  __builtin_amdgcn_wave_barrier();
+  double tr = (int)threadIdx.x < K ? S[li * LD + li] : 0.0;
+  tr = wave_sum(tr);
+  double lam = shift * tr / K;
+  const bool zero = !(lam > 0.0);
+  bool bad = true;
+  for (int attempt = 0; attempt < 8 && bad && !zero; ++attempt) {
+    if (attempt) lam *= 100.0;
+    bad = !factor_diag<N>(S, LD, 0, K, lam, D, dinv, prow);
+  }
+  if (bad && threadIdx.x == 0 && !(FULL && zero)) atomicAdd(nfail, 1);
+  __builtin_amdgcn_wave_barrier();
+  double p[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) p[i] = i == li ? 1.0 : 0.0;
+  if (!bad) {
+#pragma unroll
+    for (int i = N - 1; i >= 0; --i) {
+      p[i] *= dinv[i];
+#pragma unroll
+      for (int q = 0; q < i; ++q) p[q] -= D[q * LD + i] * p[i];
+    }
+  }
+  if (threadIdx.x >= K) return;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if (i >= K) break;
+    if constexpr (FULL) {
+      X[(int64_t)b * K * K + i * K + li] = p[i];
+      rinvT[(int64_t)b * K * K + li * K + i] = p[i];
+    } else if (i <= li) {
+      rc[foff[b] + li * (li + 1) / 2 + i] = p[i];
+    }
+  }
+}
+
 template <int NW, int NC, bool FULL>
 static hipError_t factor_launch(const DevBlock* blocks, int blk0, int64_t n_blocks, int kmax,
                                 const double* G, double* W, double* X, const int64_t* goff,
                                 const int64_t* foff, double shift, double* rc, double* rinvT,
                                 int32_t* nfail, hipStream_t s) {
-  if (n_blocks == 0) return hipSuccess;
   constexpr int pw = 16 * NW * NC + 8;
   const size_t lds = (size_t)16 * pw * sizeof(double);
   if (lds > 48 * 1024) {
@@ -396,14 +454,25 @@ static hipError_t factor_launch(const DevBlock* blocks, int blk0, int64_t n_bloc
   return hipGetLastError();
 }
 
-// Four wavefronts of two tiles to 128 columns (several workgroups a CU overlap the sequential
-// steps), eight of two to 256 and of four to 512.
+// One wavefront to 16 columns, and to 24 where that gives no more than one to a SIMD (it takes all
+// registers: 256 blocks of K = 20 66 against 72 us, 4,096 313 against 295); four of two tiles to 128
+// columns (several workgroups a CU overlap the sequential steps), eight of two to 256 and of four to
+// 512.
 template <bool FULL>
 static hipError_t factor_by_width(const DevBlock* blocks, int blk0, int64_t n_blocks, int kmax,
                                   const double* G, double* W, double* X, const int64_t* goff,
                                   const int64_t* foff, double shift, double* rc, double* rinvT,
                                   int32_t* nfail, hipStream_t s) {
   if (kmax < 1 || kmax > kPatchMaxK) return hipErrorInvalidValue;
+  if (n_blocks == 0) return hipSuccess;
+  if (kmax <= 16 || (kmax <= 24 && n_blocks <= 1024)) {
+    const auto tile = kmax <= 4    ? k_bj_factor_tile<FULL, 4>
+                      : kmax <= 16 ? k_bj_factor_tile<FULL, 16>
+                                   : k_bj_factor_tile<FULL, 24>;
+    hipLaunchKernelGGL(tile, dim3((unsigned)n_blocks), dim3(64), 0, s, blocks, blk0, kmax, G, X, goff,
+                       foff, shift, rc, rinvT, nfail);
+    return hipGetLastError();
+  }
   const auto launch = kmax <= 128   ? factor_launch<4, 2, FULL>
                       : kmax <= 256 ? factor_launch<8, 2, FULL>
                                     : factor_launch<8, 4, FULL>;

@@ -198,9 +198,9 @@ hipError_t launch_bt_bj_recover(const DevBlock* blocks, int64_t n_blocks, const 
 hipError_t launch_bt_axpy(int64_t n, const double* y, double* x, hipStream_t s);
 hipError_t launch_bt_recover_plain(int64_t n, const double* y, const double* x0, double* x,
                                    hipStream_t s);
-// two_panels: some task lies off the diagonal (blocks of more than 128 columns)
+// kmax: the blocks' largest nk (above 128 some tasks lie off the diagonal)
 hipError_t launch_bt_gram_diag(const DevBlock* blocks, const GramTask* tasks, int64_t n_tasks,
-                               bool two_panels, const double* A, const int64_t* goff, double* G,
+                               int kmax, const double* A, const int64_t* goff, double* G,
                                hipStream_t s);
 // factors of blocks blk0 .. blk0 + n_blocks - 1 (k_factor.hip); kmax: their largest nk (<=
 // kPatchMaxK).  W: scratch beside G (both nk x nk at goff); G is overwritten
