@@ -21,23 +21,26 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
 }
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
-// Workgroup tile 64 x 64, k in stages of 128; LDS rows padded by 16 bytes (the operand reads of a
-// wavefront then spread evenly over the banks).
-constexpr int kMT = 64, kNT = 64, kKT = 128, kLdsK = kKT + 8;
+// Workgroup tile 64 x 64, k in stages of KT = 128 or, for short products, 32; LDS rows padded by 16
+// bytes (the operand reads of a wavefront then spread evenly over the banks).
+constexpr int kMT = 64, kNT = 64, kKT = 128, kShortK = 32;
 
 typedef uint16_t u16x4_t __attribute__((ext_vector_type(4)));
 typedef uint16_t u16x8_t __attribute__((ext_vector_type(8)));
 
-// How a 64 x 128 (rows x k) operand tile X(row, k) = P[row sr + k sk] is staged into rows of
-// consecutive k: each thread takes four groups of 8 elements, consecutive k of a row (OP_K) or
-// consecutive rows at each of four consecutive k (OP_M: rows contiguous in memory), a 16-byte load
+// How a 64 x KT (rows x k) operand tile X(row, k) = P[row sr + k sk] is staged into rows of
+// consecutive k: each thread takes KT / 32 groups of 8 elements, consecutive k of a row (OP_K) or
+// consecutive rows at each of as many consecutive k (OP_M: rows contiguous in memory), a 16-byte load
 // each where `vec` says that the groups are aligned and the group lies within the operand.
 enum { OP_K = 0, OP_M = 1 };
 
-template <int MODE>
+template <int MODE, int KT>
 __device__ __forceinline__ void tile_place(int v, int* row, int* k) {
   const int t = threadIdx.x;
-  if constexpr (MODE == OP_K) {
+  if constexpr (KT == kShortK) {
+    *row = MODE == OP_K ? t >> 2 : 8 * (t & 7);
+    *k = MODE == OP_K ? 8 * (t & 3) : t >> 3;
+  } else if constexpr (MODE == OP_K) {
     *row = (t >> 4) + 16 * v;
     *k = 8 * (t & 15);
   } else {   // per wavefront 4 groups of rows (64 contiguous bytes) x 64 k (two-way LDS banks)
@@ -46,14 +49,14 @@ __device__ __forceinline__ void tile_place(int v, int* row, int* k) {
   }
 }
 
-template <int MODE>
+template <int MODE, int KT>
 __device__ __forceinline__ void tile_load(const uint16_t* __restrict__ P, int64_t sr, int64_t sk,
                                           bool vec, int rows, int K, int r0, int k0,
-                                          u16x8_t (&r)[4]) {
+                                          u16x8_t (&r)[KT / 32]) {
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
+  for (int v = 0; v < KT / 32; ++v) {
     int row, k;
-    tile_place<MODE>(v, &row, &k);
+    tile_place<MODE, KT>(v, &row, &k);
     row += r0;
     k += k0;
     const uint16_t* q = P + (int64_t)row * sr + (int64_t)k * sk;
@@ -69,21 +72,22 @@ __device__ __forceinline__ void tile_load(const uint16_t* __restrict__ P, int64_
   }
 }
 
-template <int MODE>
-__device__ __forceinline__ void tile_store(uint16_t (*S)[kLdsK], const u16x8_t (&r)[4]) {
+template <int MODE, int KT>
+__device__ __forceinline__ void tile_store(uint16_t (*S)[KT + 8], const u16x8_t (&r)[KT / 32]) {
+  int row, k;
   if constexpr (MODE == OP_K) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      int row, k;
-      tile_place<MODE>(v, &row, &k);
+    for (int v = 0; v < KT / 32; ++v) {
+      tile_place<MODE, KT>(v, &row, &k);
       *reinterpret_cast<u16x8_t*>(&S[row][k]) = r[v];
     }
   } else {
-    int row, k;
-    tile_place<MODE>(0, &row, &k);
+    tile_place<MODE, KT>(0, &row, &k);
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-      *reinterpret_cast<u16x4_t*>(&S[row + e][k]) = u16x4_t{r[0][e], r[1][e], r[2][e], r[3][e]};
+    for (int e = 0; e < 8; ++e) {
+      if constexpr (KT == kShortK) S[row + e][k] = r[0][e];
+      else *reinterpret_cast<u16x4_t*>(&S[row + e][k]) = u16x4_t{r[0][e], r[1][e], r[2][e], r[3][e]};
+    }
   }
 }
 
@@ -167,6 +171,20 @@ __device__ __forceinline__ void get_row(uint16_t (&x)[16], const uint16_t* __res
   }
 }
 
+// The epilogue of one element.
+__device__ __forceinline__ void put_one(const MlpGemm& p, int S, float* __restrict__ ws, int m, int n,
+                                        float c) {
+  const int64_t o = (int64_t)m * p.ldo + n;
+  if (S > 1) ws[((int64_t)blockIdx.z * p.M + m) * p.N + n] = c;
+  else if (p.epi == MLP_EPI_F32) p.out_f32[o] = c;
+  else if (p.epi == MLP_EPI_BIAS) p.out_f32[o] = c + p.bias[n];
+  else if (p.epi == MLP_EPI_BIAS_TANH) p.out_bf16[o] = f32_to_bf16(tanhf(c + p.bias[n]));
+  else {   // MLP_EPI_DTANH
+    const float a = bf16_to_f32(p.act[o]);
+    p.out_bf16[o] = f32_to_bf16(c * (1.0f - a * a));
+  }
+}
+
 // C[M][N] = sum_k A(m, k) B(k, n), A(m, k) = A[m sam + k sak], B(k, n) = B[k sbk + n sbn]
 // (bfloat16), then the epilogue.  Four waves of 32 x 32 (2 x 2 tiles of v_mfma_f32_16x16x32_bf16),
 // k through two LDS buffers (rows of A and columns of B with k contiguous, each lane's operand one
@@ -179,7 +197,7 @@ __device__ __forceinline__ void get_row(uint16_t (&x)[16], const uint16_t* __res
 // [z kc, (z + 1) kc) and writes its FP32 partial tile to ws[z][M][N]; k_mlp_gemm_reduce sums them
 // in order and applies the epilogue.  The workgroups of z >= S, if any, form the column sums of A^T
 // (p.colsum), one task each.
-template <int MA, int MB>
+template <int MA, int MB, int KT>
 __global__ void __launch_bounds__(256) k_mlp_gemm(MlpGemm p, bool va, bool vb, int kc, int S,
                                                   float* __restrict__ ws) {
   extern __shared__ __align__(16) uint16_t mlp_lds[];
@@ -190,7 +208,7 @@ __global__ void __launch_bounds__(256) k_mlp_gemm(MlpGemm p, bool va, bool vb, i
     if (id < colsum_tasks(p.K, p.M)) column_sums(p.A, p.K, p.M, va, id, p.colpart, mlp_lds);
     return;
   }
-  typedef uint16_t Buf[kMT + kNT][kLdsK];
+  typedef uint16_t Buf[kMT + kNT][KT + 8];
   Buf* const T = reinterpret_cast<Buf*>(mlp_lds);   // [2]: rows of A, then columns of B
   id = xcd_tile(id, tiles);
   const int m0 = id / nx * kMT, n0 = id % nx * kNT;
@@ -204,30 +222,30 @@ __global__ void __launch_bounds__(256) k_mlp_gemm(MlpGemm p, bool va, bool vb, i
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f4v_t{0.f, 0.f, 0.f, 0.f};
-  u16x8_t ra[4][4], rb[4][4];
+  u16x8_t ra[4][KT / 32], rb[4][KT / 32];
   // operand B is staged as its transpose: rows n, X(n, k) = B[k sbk + n sbn]
 #pragma unroll
   for (int u = 0; u < 3; ++u)
-    if (kb + u * kKT < ke) {
-      tile_load<MA>(p.A, p.sam, p.sak, va, p.M, ke, m0, kb + u * kKT, ra[u]);
-      tile_load<MB>(p.B, p.sbn, p.sbk, vb, p.N, ke, n0, kb + u * kKT, rb[u]);
+    if (kb + u * KT < ke) {
+      tile_load<MA, KT>(p.A, p.sam, p.sak, va, p.M, ke, m0, kb + u * KT, ra[u]);
+      tile_load<MB, KT>(p.B, p.sbn, p.sbk, vb, p.N, ke, n0, kb + u * KT, rb[u]);
     }
-  for (int k4 = kb; k4 < ke; k4 += 4 * kKT) {
+  for (int k4 = kb; k4 < ke; k4 += 4 * KT) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int k0 = k4 + u * kKT;
+      const int k0 = k4 + u * KT;
       if (k0 < ke) {
         // the buffer's last readers passed the barrier of the stage between
         Buf& Sb = T[u & 1];
-        tile_store<MA>(Sb, ra[u]);
-        tile_store<MB>(Sb + kMT, rb[u]);
-        if (k0 + 3 * kKT < ke) {
-          tile_load<MA>(p.A, p.sam, p.sak, va, p.M, ke, m0, k0 + 3 * kKT, ra[(u + 3) & 3]);
-          tile_load<MB>(p.B, p.sbn, p.sbk, vb, p.N, ke, n0, k0 + 3 * kKT, rb[(u + 3) & 3]);
+        tile_store<MA, KT>(Sb, ra[u]);
+        tile_store<MB, KT>(Sb + kMT, rb[u]);
+        if (k0 + 3 * KT < ke) {
+          tile_load<MA, KT>(p.A, p.sam, p.sak, va, p.M, ke, m0, k0 + 3 * KT, ra[(u + 3) & 3]);
+          tile_load<MB, KT>(p.B, p.sbn, p.sbk, vb, p.N, ke, n0, k0 + 3 * KT, rb[(u + 3) & 3]);
         }
         __syncthreads();
 #pragma unroll
-        for (int ks = 0; ks < kKT; ks += 32) {
+        for (int ks = 0; ks < KT; ks += 32) {
           if (k0 + ks >= ke) break;
           bf8v_t a[2], b[2];
 #pragma unroll
@@ -242,6 +260,20 @@ __global__ void __launch_bounds__(256) k_mlp_gemm(MlpGemm p, bool va, bool vb, i
               acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
         }
       }
+    }
+  }
+  if constexpr (KT == kShortK) {
+    if (p.M < kMT) {   // few rows: their elements one by one, over all lanes that hold any
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int m = wm * 32 + i * 16 + 4 * lq + v, n = n0 + wn * 32 + j * 16 + li;
+            if (m < p.M && n < p.N) put_one(p, S, ws, m, n, acc[i][j][v]);
+          }
+      return;
     }
   }
   // the tile through LDS (lane holds column li, rows 4 lq + v of an accumulator), so that a thread
@@ -446,7 +478,13 @@ hipError_t launch_mlp_gemm(const MlpGemm& p, float* ws, hipStream_t s) {
   const int64_t tiles = (int64_t)nx * ny;
   const int nz = p.colsum ? (int)((colsum_tasks(p.K, p.M) + tiles - 1) / tiles) : 0;
   const dim3 grid((unsigned)nx, (unsigned)ny, (unsigned)(S + nz));
-  const size_t lds = 2 * (kMT + kNT) * kLdsK * sizeof(uint16_t);   // 68 KB
+  // up to 64 k in stages of 32: a stage of 128 of which half is there takes longer to load and store
+  // (predictions of one row through widths 4, 16, 16, 8 26.1 against 35.8 us, of 4,096 rows through 4,
+  // 48, 16 28.7 against 31.4; a layer of 64 rows, 64 by 64, 4.2 against 5.2)
+  const bool sh = kc <= 2 * kShortK;
+  // two stages (68 KB), in short ones at least a task of the column sums
+  const size_t lds = sh ? (size_t)kColRows * 64 * sizeof(uint16_t)
+                        : 2 * (kMT + kNT) * (kKT + 8) * sizeof(uint16_t);
   const bool am = p.sak != 1 && p.sam == 1, bm = p.sbk != 1 && p.sbn == 1;
   const bool va = aligned16(p.A) && (am ? p.sak % 8 == 0 : p.sak == 1 && p.sam % 8 == 0);
   const bool vb = aligned16(p.B) && (bm ? p.sbk % 8 == 0 : p.sbk == 1 && p.sbn % 8 == 0);
@@ -454,10 +492,14 @@ hipError_t launch_mlp_gemm(const MlpGemm& p, float* ws, hipStream_t s) {
   hipError_t e = hipSuccess;
 #define GEMM(A_, B_)                                                                             \
   do {                                                                                           \
-    e = hipFuncSetAttribute((const void*)k_mlp_gemm<A_, B_>,                                     \
+    if (sh) {                                                                                    \
+      hipLaunchKernelGGL((k_mlp_gemm<A_, B_, kShortK>), grid, dim3(256), lds, s, p, va, vb, kc, S, w); \
+      break;                                                                                     \
+    }                                                                                            \
+    e = hipFuncSetAttribute((const void*)k_mlp_gemm<A_, B_, kKT>,                                \
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);               \
     if (e != hipSuccess) return e;                                                               \
-    hipLaunchKernelGGL((k_mlp_gemm<A_, B_>), grid, dim3(256), lds, s, p, va, vb, kc, S, w);      \
+    hipLaunchKernelGGL((k_mlp_gemm<A_, B_, kKT>), grid, dim3(256), lds, s, p, va, vb, kc, S, w);  \
   } while (0)
   if (am) { if (bm) GEMM(OP_M, OP_M); else GEMM(OP_M, OP_K); }
   else { if (bm) GEMM(OP_K, OP_M); else GEMM(OP_K, OP_K); }
