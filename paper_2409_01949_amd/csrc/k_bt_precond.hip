@@ -17,8 +17,10 @@ typedef double d4_t __attribute__((ext_vector_type(4)));
 // One square of G_b (a GramTask: rows i0.., columns j0.., at most 128 each; on the diagonal the
 // tiles I <= J), FP64, over all points of the block (gram_product).  8,192 blocks of K = 64 to 128
 // 1,944 -> 955 us, patches of up to 512 columns (16 instances) 1,741 -> 958 us, against tiles dealt
-// with a search per product and stages of 32 points without prefetch.  WT: squares of 32 WT columns
-// for the batch's widest block (the staging of 128 rows was the time of narrow blocks).
+// with a search per product and stages of 32 points without prefetch.  On the diagonal a block
+// takes the square of 32, 64 or 128 columns that holds it, WT being that of the batch's widest (the
+// staging of 128 rows was the time of narrow blocks: 16 of K = 33 and one of K = 4 on 1,600 points 205
+// us a precondition call, 120 so).
 template <int WT>
 __global__ void __launch_bounds__(256) k_bt_gram_diag(const DevBlock* __restrict__ blocks,
                                                       const GramTask* __restrict__ tasks,
@@ -41,8 +43,13 @@ __global__ void __launch_bounds__(256) k_bt_gram_diag(const DevBlock* __restrict
   R.v1 = B.n;
   double* out = G + goff[T.blk] + (int64_t)T.i0 * K + T.j0;
   auto put = [&](int r, int c, double v) { out[r * K + c] = v; };
-  if (T.i0 == T.j0) gram_product<ELMFB_FP64, WT, GRAM_UPPER>(R, gd_lds, put);
-  else if constexpr (WT == 4) gram_product<ELMFB_FP64, 4, GRAM_SQUARE>(R, gd_lds, put);
+  if (T.i0 == T.j0) {
+    if (WT == 1 || R.nx <= 32) gram_product<ELMFB_FP64, 1, GRAM_UPPER>(R, gd_lds, put);
+    else if (WT == 2 || R.nx <= 64) gram_product<ELMFB_FP64, 2, GRAM_UPPER>(R, gd_lds, put);
+    else if constexpr (WT == 4) gram_product<ELMFB_FP64, 4, GRAM_UPPER>(R, gd_lds, put);
+  } else if constexpr (WT == 4) {
+    gram_product<ELMFB_FP64, 4, GRAM_SQUARE>(R, gd_lds, put);
+  }
 }
 
 // Fold the preconditioner into the matrix: Mhat_b = M_b R_b^{-1}, i.e. in the feature-major
