@@ -259,7 +259,7 @@ __device__ __forceinline__ double quad_f64(const typename Quad<PREC>::t& x, int 
 // for the largest block).  Without runs a workgroup takes a whole block; with runs (patch blocks,
 // several hundred points over up to 512 columns) it takes one run of at most 256 points, so its
 // four waves get one 64-point group each (runs of a block are dealt to one XCD; blk = -1 pads).
-// FP64 entries; the narrow copies take k_bt_mvb_narrow.
+// FP64 entries, and the narrow copies where k_bt_mvb_narrow is not faster (mvb_on_matrix_cores).
 template <int PREC, int FA>
 __global__ void __launch_bounds__(256) k_bt_mvb(const DevBlock* __restrict__ blocks,
                                                 const Tile* __restrict__ runs,
@@ -310,7 +310,7 @@ __global__ void __launch_bounds__(256) k_bt_mvb(const DevBlock* __restrict__ blo
 
 typedef double bt_d4 __attribute__((ext_vector_type(4)));
 
-// The narrow copies' pass on v_mfma_f64_16x16x4_f64: 16 points x 4 features by 4 features x 8 right-
+// The narrow copies' pass over many blocks on v_mfma_f64_16x16x4_f64: 16 points x 4 features by 4 features x 8 right-
 // hand sides (the other 8 columns repeat them).  A wavefront takes 64 points, lane (li, lq) the
 // four points 4 li .. of feature 4 s + lq, which feed four products with one coefficient read from
 // LDS; on the vector units every entry takes four 16-byte reads of the coefficients, which bounds
@@ -1005,23 +1005,43 @@ hipError_t launch_bt_rhs(const Geo* geos, const InstInfo* insts, const RowTile* 
   return hipGetLastError();
 }
 
-template <int FA>
-static void mvb_fa(int prec, dim3 grid, size_t lds, const DevBlock* blocks, const Tile* runs,
-                   const void* A, const double* v, int R, const SolveState* st, double* tpart,
-                   hipStream_t s) {
-  const dim3 blk(256);
-  if (prec == ELMFB_FP32)
-    hipLaunchKernelGGL((k_bt_mvb_narrow<ELMFB_FP32, FA>), grid, blk, lds, s, blocks, runs, A, v, R, st,
-                       tpart);
-  else if (prec == ELMFB_BF16)
-    hipLaunchKernelGGL((k_bt_mvb_narrow<ELMFB_BF16, FA>), grid, blk, lds, s, blocks, runs, A, v, R, st,
-                       tpart);
-  else if (prec == ELMFB_FP16)
-    hipLaunchKernelGGL((k_bt_mvb_narrow<ELMFB_FP16, FA>), grid, blk, lds, s, blocks, runs, A, v, R, st,
-                       tpart);
-  else
-    hipLaunchKernelGGL((k_bt_mvb<ELMFB_FP64, FA>), grid, blk, lds, s, blocks, runs, A, v, R, st,
-                       tpart);
+// Narrow copies on the matrix cores (k_bt_mvb_narrow) or the vector units (k_bt_mvb): the same bits, so
+// by time alone.  The matrix cores' form needs workgroups to hide its shorter loads ahead, and reads
+// fewer coefficients but multiplies by 16 right-hand sides whatever R, which pays with wide blocks or
+// many right-hand sides.  FP32, vector -> matrix, us, R = 1 / 8:
+//   8,192 blocks K = 100 272 -> 242 / 314 -> 276, 64 171 -> 157 / 196 -> 177, 33 91 -> 92 / 126 -> 109,
+//     16 44 -> 49 / 98 -> 69, 4 19 -> 27 / 65 -> 33
+//   2,048 blocks K = 100 75 -> 63 / 85 -> 74, 48 37 -> 35 / 39 -> 37, 33 27 -> 29 / 30 -> 31, 24 20 -> 21 /
+//     25 -> 23, 8 8.6 -> 11 / 21 -> 14
+//   256 blocks K = 100 23 -> 26 / 24 -> 26, 64 11 -> 13 / 13 -> 16, 33 6.8 -> 8.7 / 9.0 -> 9.1
+static bool mvb_on_matrix_cores(int64_t n_grid, int kmax, int R) {
+  if (kmax >= 48) return n_grid >= 1024;
+  return R > 4 && n_grid >= (kmax > 24 ? 4096 : 1024);
+}
+
+template <int PREC, int FA>
+static void mvb_launch(int64_t n_grid, int kmax, const DevBlock* blocks, const Tile* runs, const void* A,
+                       const double* v, int R, const SolveState* st, double* tpart, hipStream_t s) {
+  const dim3 grid((unsigned)n_grid), blk(256);
+  const size_t lds = (size_t)(kmax + 3) / 4 * 4 * kMaxRhs * sizeof(double);
+  if constexpr (PREC != ELMFB_FP64) {
+    if (mvb_on_matrix_cores(n_grid, kmax, R)) {
+      hipLaunchKernelGGL((k_bt_mvb_narrow<PREC, FA>), grid, blk, lds, s, blocks, runs, A, v, R, st, tpart);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_bt_mvb<PREC, FA>), grid, blk, lds, s, blocks, runs, A, v, R, st, tpart);
+}
+
+template <int PREC>
+static hipError_t mvb_ahead(int fa, int64_t n_grid, int kmax, const DevBlock* blocks, const Tile* runs,
+                            const void* A, const double* v, int R, const SolveState* st,
+                            double* tpart, hipStream_t s) {
+  if (fa == 4) mvb_launch<PREC, 4>(n_grid, kmax, blocks, runs, A, v, R, st, tpart, s);
+  else if (fa == 8) mvb_launch<PREC, 8>(n_grid, kmax, blocks, runs, A, v, R, st, tpart, s);
+  else if (fa == 16) mvb_launch<PREC, 16>(n_grid, kmax, blocks, runs, A, v, R, st, tpart, s);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 hipError_t launch_bt_mvb(int prec, const DevBlock* blocks, const Tile* runs, int64_t n_grid,
@@ -1029,13 +1049,11 @@ hipError_t launch_bt_mvb(int prec, const DevBlock* blocks, const Tile* runs, int
                          double* tpart, hipStream_t s, int fa) {
   if (n_grid == 0) return hipSuccess;
   if (kmax < 1 || kmax > kPatchMaxK) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)n_grid);
-  const size_t lds = (size_t)(kmax + 3) / 4 * 4 * kMaxRhs * sizeof(double);
-  if (fa == 4) mvb_fa<4>(prec, grid, lds, blocks, runs, A, v, R, st, tpart, s);
-  else if (fa == 8) mvb_fa<8>(prec, grid, lds, blocks, runs, A, v, R, st, tpart, s);
-  else if (fa == 16) mvb_fa<16>(prec, grid, lds, blocks, runs, A, v, R, st, tpart, s);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
+  const auto f = prec == ELMFB_FP32   ? mvb_ahead<ELMFB_FP32>
+                 : prec == ELMFB_BF16 ? mvb_ahead<ELMFB_BF16>
+                 : prec == ELMFB_FP16 ? mvb_ahead<ELMFB_FP16>
+                                      : mvb_ahead<ELMFB_FP64>;
+  return f(fa, n_grid, kmax, blocks, runs, A, v, R, st, tpart, s);
 }
 
 hipError_t launch_bt_gather(const Geo* geos, const InstInfo* insts, const DevBlock* blocks,
