@@ -128,13 +128,14 @@ __global__ void __launch_bounds__(64 * kEvWaves) k_evaluate(Geo g, const double*
         }
         __builtin_amdgcn_wave_barrier();
         int c = c0, k = k0;
+        double lev = 0.0;                // a level at a time: fewer terms to a running sum
         while (c < nc) {
           const EvBlock B = list[c];
           if (B.q0 >= 0) {
             const int64_t q = B.q0 + k;
             const double2 wq = reinterpret_cast<const double2*>(W)[q];
             const double z = wq.x * B.xb + wq.y * B.yb + bias[q];
-            total += B.w * (coef[q] * table_tanh(z, tt));
+            lev += B.w * (coef[q] * table_tanh(z, tt));
           }
           c += dq;
           k += dr;
@@ -143,6 +144,7 @@ __global__ void __launch_bounds__(64 * kEvWaves) k_evaluate(Geo g, const double*
             ++c;
           }
         }
+        total += lev;
         __builtin_amdgcn_wave_barrier();
       }
     }
