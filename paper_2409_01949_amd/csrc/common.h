@@ -170,9 +170,8 @@ struct SolveState {
   double su, sv;           // scale of the stored (unnormalised) u and v
   double rhobar, phibar;
   double anorm, bnorm, xnorm, rnorm, arnorm;
-  double t1, t2;           // x += t1 w, w = v + t2 w
-  double gamma;            // CGLS: ||s||^2
-  double cg_a, cg_b;       // CGLS step sizes
+  double t1, t2;           // x += t1 w, w = v + t2 w (batches, one-workgroup LSQR)
+  double gamma;            // CGLS: ||s||^2; CG on Gram blocks: r . z
   double rel_l2;           // last solution-error check
   double atol, btol;
   double target;           // rel-L2 target (0: off)
@@ -192,56 +191,7 @@ struct BtOuter {
   int32_t done, outer, iters, istop;
 };
 
-// Convert an FP64 value to the bits of a 16-bit IEEE-style format with MB stored significand
-// bits and EB exponent bits (bias 2^(EB-1) - 1) by round-to-nearest-even in one step: keep
-// MB + 1 significant bits, or the fixed spacing 2^(emin - MB) below 2^emin; overflow to
-// infinity.  bfloat16 is <7, 8>, IEEE binary16 is <10, 5>.
-template <int MB, int EB>
-__host__ __device__ inline uint16_t f64_to_small_rne(double x) {
-  constexpr int kEmax = (1 << (EB - 1)) - 1;       // also the bias
-  constexpr int kEmin = 1 - kEmax;
-  constexpr int kSub = kEmin - MB;                 // exponent of the subnormal spacing
-  constexpr uint64_t kMant = (1ull << MB) - 1;
-  constexpr uint64_t kInf = ((1ull << EB) - 1) << MB;
-  union { double d; uint64_t u; } dv;
-  dv.d = x;
-  const uint64_t sign = (dv.u >> 63) << 15;
-  const uint64_t mag = dv.u & 0x7fffffffffffffffull;
-  if (mag >= 0x7ff0000000000000ull) {               // inf or nan
-    if (mag > 0x7ff0000000000000ull) return (uint16_t)(sign | kInf | (1ull << (MB - 1)));
-    return (uint16_t)(sign | kInf);
-  }
-  const int e = (int)(mag >> 52);                    // biased FP64 exponent
-  const uint64_t frac = mag & 0xfffffffffffffull;
-  const int exp2v = (e == 0) ? -1022 : e - 1023;
-  const uint64_t sig = (e == 0) ? frac : (frac | (1ull << 52));   // value = sig 2^(exp2v-52)
-  int ulp_e = exp2v - MB;                            // spacing of the target at this binade
-  if (ulp_e < kSub) ulp_e = kSub;
-  const int sh = ulp_e - exp2v + 52;                 // q = sig / 2^sh, rounded
-  uint64_t q, rem, half;
-  if (sh >= 64) {
-    return (uint16_t)sign;                           // far below half the smallest spacing
-  } else if (sh <= 0) {
-    q = sig << (-sh); rem = 0; half = 1;
-  } else {
-    q = sig >> sh;
-    rem = sig & ((1ull << sh) - 1);
-    half = 1ull << (sh - 1);
-  }
-  if (rem > half || (rem == half && (q & 1))) q += 1;
-  if (q == 0) return (uint16_t)sign;
-  // q is an integer multiple of 2^ulp_e; find the binade of q 2^ulp_e and rebuild the bits
-  const int msb = 63 - __builtin_clzll(q);
-  const int vexp = ulp_e + msb;
-  if (vexp < kEmin) return (uint16_t)(sign | (q & kMant));     // subnormal: exponent field 0
-  if (vexp > kEmax) return (uint16_t)(sign | kInf);
-  const uint64_t mant = (msb >= MB) ? (q >> (msb - MB)) : (q << (MB - msb));
-  return (uint16_t)(sign | ((uint64_t)(vexp + kEmax) << MB) | (mant & kMant));
-}
-
-__host__ __device__ inline uint16_t f64_to_bf16_rne(double x) { return f64_to_small_rne<7, 8>(x); }
-__host__ __device__ inline uint16_t f64_to_fp16_rne(double x) { return f64_to_small_rne<10, 5>(x); }
-
+// The value of a bfloat16.
 __host__ __device__ inline double bf16_to_f64(uint16_t b) {
   union { float f; uint32_t u; } v;
   v.u = ((uint32_t)b) << 16;

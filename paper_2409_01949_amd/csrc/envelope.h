@@ -115,7 +115,7 @@ __device__ __forceinline__ void store_entry<ELMFB_FP32>(void* A, int64_t i, doub
 }
 // The 16-bit stores round to odd at 24 bits first (the dropped bits or'ed into the last kept one),
 // which FP32 holds exactly: the second rounding then sees which side of every tie the FP64 value
-// lies on, so the result is the single rounding of f64_to_*_rne in a few instructions.
+// lies on, so the result is that of one rounding to nearest even, in a few instructions.
 __device__ __forceinline__ float round_to_odd_f32(double v) {
   const uint64_t u = __double_as_longlong(v);
   const uint64_t odd = (u & 0x1fffffffull) ? 0x20000000ull : 0;

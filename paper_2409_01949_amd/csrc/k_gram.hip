@@ -125,11 +125,6 @@ static hipError_t gram_launch(const Geo& g, const DevBlock* blocks, const GramPa
   const int wt = gram_square(g.K) / 32, nsq = (g.K + 32 * wt - 1) / (32 * wt);
   const dim3 grid((unsigned)n_chunks, (unsigned)(nsq * nsq));
   const size_t sm = (size_t)2 * 32 * wt * kGrStride * sizeof(gr_vec);
-  if (wt == 4) {   // 68 KB
-    const hipError_t e = hipFuncSetAttribute((const void*)k_gram<PREC, 4>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm);
-    if (e != hipSuccess) return e;
-  }
 #define GRAM(W)                                                                                  \
   hipLaunchKernelGGL((k_gram<PREC, W>), grid, dim3(256), sm, s, g, blocks, pairs, chunks,        \
                      chunk_vecs, A, (out_t*)G, (out_t*)part)

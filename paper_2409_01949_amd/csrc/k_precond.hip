@@ -150,7 +150,7 @@ __global__ void __launch_bounds__(256) k_bj_recover(Geo g, const double* __restr
 }
 
 // The middle of a preconditioned CG step on the Gram blocks, one subdomain block per workgroup:
-// cg_a = gamma / (p . q) as in k_gcg_update, a += cg_a p ; r -= cg_a q, then, as r is the block's
+// al = gamma / (p . q) as in k_gcg_update, a += al p ; r -= al q, then, as r is the block's
 // own, z = R^{-1} (R^{-T} r) through LDS and the partials of r . r and r . z.  The sums of z run as in
 // k_bj_apply_t and k_bj_apply, whose launches this saves.  Bound by latency (launches, then the
 // chain of sums); KB: K rounded up to 64 or 128; up to 64 both factors' entries are loaded before
@@ -210,7 +210,6 @@ __global__ void __launch_bounds__(256) k_gcg_block(
   const bool ok = pq > 0.0;
   const double al = ok ? gamma / pq : 0.0;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    st->cg_a = al;
     st->gamma = gamma;
     if (!ok) {
       st->istop = 3;

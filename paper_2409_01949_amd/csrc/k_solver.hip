@@ -1,7 +1,7 @@
 // Krylov recurrences on the device: LSQR (Paige & Saunders 1982, damp = 0, no condition limit;
-// the method's solver, Sec. 4.1) and CGLS.  All scalars live in a device SolveState and every
-// scalar update runs in one workgroup, so the iteration loop needs no host round trip and can
-// be captured in a hipGraph.  Norms are reduced in a fixed order (deterministic).  The stored
+// the method's solver, Sec. 4.1) and CGLS.  All scalars live in a device SolveState, formed by
+// every workgroup that uses them and recorded by one, so the iteration loop needs no host round
+// trip and can be captured in a hipGraph.  Norms are reduced in a fixed order (deterministic).  The stored
 // u and v are kept unnormalised with their scales su = 1/beta and sv = 1/alpha; consumers apply
 // the scale as they read.
 #include "device.h"
@@ -135,8 +135,6 @@ __global__ void __launch_bounds__(256) k_lsqr_update(Geo g, double* __restrict__
     st->next_alpha = alpha;
     st->next_sv = sv;
     st->next_rhobar = -c * alpha;
-    st->t1 = t1;
-    st->t2 = t2;
     st->rnorm = phibar;   // and the next phibar
     st->arnorm = alpha * fabs(c) * phibar;
   }
@@ -207,7 +205,7 @@ __global__ void __launch_bounds__(256) k_cgls_init(SolveState* st, const double*
   }
 }
 
-// cg_a = gamma / ||A p||^2 from its n partials, then x += cg_a p ; r -= cg_a t (t = A p) ; partial
+// a = gamma / ||A p||^2 from its n partials, then x += a p ; r -= a t (t = A p) ; partial
 // ||r||^2.
 __global__ void __launch_bounds__(256) k_cgls_update(Geo g, double* __restrict__ x,
                                                      const double* __restrict__ p,
@@ -220,7 +218,6 @@ __global__ void __launch_bounds__(256) k_cgls_update(Geo g, double* __restrict__
   const double gamma = st->next_gamma;
   const double a = gamma / reduce_partials_all(red_t, n, sh);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    st->cg_a = a;
     st->gamma = gamma;
   }
   const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -237,7 +234,7 @@ __global__ void __launch_bounds__(256) k_cgls_update(Geo g, double* __restrict__
   if (threadIdx.x == 0) red[blockIdx.x] = s;
 }
 
-// The end of a step: ||r||, gamma = ||s||^2, cg_b, the stopping tests, and p = s + cg_b p (p is not
+// The end of a step: ||r||, b = ||s||^2 / gamma, the stopping tests, and p = s + b p (p is not
 // used after the step that stopped).
 __global__ void __launch_bounds__(256) k_cgls_update_p(Geo g, double* __restrict__ p,
                                                        const double* __restrict__ s,
@@ -253,7 +250,6 @@ __global__ void __launch_bounds__(256) k_cgls_update_p(Geo g, double* __restrict
     __syncthreads();
     const double sr = reduce_partials(red_r, nr, sh);
     if (threadIdx.x == 0) {
-      st->cg_b = b;
       st->next_gamma = ss;
       const double rnorm = sqrt(sr);
       st->rnorm = rnorm;
@@ -368,8 +364,7 @@ hipError_t launch_cgls_update_p(const Geo& g, double* p, const double* sv, Solve
 
 // ---- CG on the assembled Gram blocks, G a = g (g = M^T h), optionally preconditioned by the
 // block-Jacobi factors (z = R^{-1} R^{-T} r, R^T R = G_jj + lambda I): Hestenes-Stiefel CG with
-// FP64 vectors and scalars.  gamma holds r.z (r.r without preconditioning), cg_a / cg_b the
-// step sizes, bnorm ||g||, rnorm ||r||.
+// FP64 vectors and scalars.  gamma holds r.z (r.r without preconditioning), bnorm ||g||, rnorm ||r||.
 
 // Start: bnorm = ||g||, rnorm = ||r0||, gamma = r0.z0; done at once when r0 = 0 or iter_lim = 0.
 __global__ void __launch_bounds__(256) k_gcg_init(SolveState* st, const double* red_b, int nb,
@@ -383,7 +378,6 @@ __global__ void __launch_bounds__(256) k_gcg_init(SolveState* st, const double* 
     st->bnorm = sqrt(bb);
     st->rnorm = sqrt(rr);
     st->gamma = st->next_gamma = rz;
-    st->cg_a = st->cg_b = 0.0;
     st->itn = 0;
     st->istop = 0;
     st->done = 0;
@@ -393,7 +387,7 @@ __global__ void __launch_bounds__(256) k_gcg_init(SolveState* st, const double* 
   }
 }
 
-// cg_a = gamma / (p . q) from the n partials of p . q, then a += cg_a p ; r -= cg_a q ; partial
+// al = gamma / (p . q) from the n partials of p . q, then a += al p ; r -= al q ; partial
 // r . r.  A breakdown (p . q <= 0: G not positive definite in this precision) stops with istop 3;
 // a workgroup that reads that `done` already has nothing to do either.
 __global__ void __launch_bounds__(256) k_gcg_update(Geo g, double* __restrict__ a,
@@ -410,7 +404,6 @@ __global__ void __launch_bounds__(256) k_gcg_update(Geo g, double* __restrict__ 
   const bool ok = pq > 0.0;
   const double al = ok ? gamma / pq : 0.0;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
-    st->cg_a = al;
     st->gamma = gamma;
     if (!ok) {
       st->istop = 3;
@@ -444,9 +437,9 @@ __global__ void __launch_bounds__(256) k_dot(const double* __restrict__ x,
   if (threadIdx.x == 0) red[blockIdx.x] = sum;
 }
 
-// The end of a step: rnorm = ||r||, gamma' = r.z (its partials red_z; NULL: z = r), cg_b =
+// The end of a step: rnorm = ||r||, gamma' = r.z (its partials red_z; NULL: z = r), b =
 // gamma'/gamma, stop on ||r|| <= btol ||g|| (istop 1) or the iteration limit (istop 7), and
-// p = z + cg_b p (p is not used after the step that stopped).
+// p = z + b p (p is not used after the step that stopped).
 __global__ void __launch_bounds__(256) k_gcg_pupdate(Geo g, double* __restrict__ p,
                                                      const double* __restrict__ z, SolveState* st,
                                                      const double* __restrict__ red_r, int nr,
@@ -464,7 +457,6 @@ __global__ void __launch_bounds__(256) k_gcg_pupdate(Geo g, double* __restrict__
     if (threadIdx.x == 0) {
       st->itn += 1;
       st->rnorm = sqrt(rr);
-      st->cg_b = b;
       st->next_gamma = rz;
       int istop = 0;
       if (st->rnorm <= st->btol * st->bnorm) istop = 1;
