@@ -107,8 +107,7 @@ __device__ __forceinline__ void gram_product(const GramRun& R, gr_vec* lds, PUT 
   const int li = lane & 15, lq = lane >> 4;
   constexpr int NR = 256 / NS, NL = 32 * WT / NR;              // rows a pass, passes
   const int slot = t % NS, f0 = t / NS;                        // staging: load, first feature row
-  // loads of a run; of one without points (an empty block, v1 = 0) a masked one, for the counts below
-  const int nv = max(1, (R.len + VE - 1) / VE);
+  const int nv = (R.len + VE - 1) / VE;                        // loads of a run, at least 1
   const int ntx = (R.nx + 15) >> 4, nty = (R.ny + 15) >> 4;
   acc_t acc[NT];
 #pragma unroll

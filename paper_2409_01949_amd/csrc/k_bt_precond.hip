@@ -38,7 +38,7 @@ __global__ void __launch_bounds__(256) k_bt_gram_diag(const DevBlock* __restrict
   R.stepx = R.stepy = 0;
   R.nx = min(kBatchMaxK, K - T.i0);
   R.ny = min(kBatchMaxK, K - T.j0);
-  R.len = B.n;
+  R.len = max(1, B.n);   // a block without points: one load, masked by v1 = 0
   R.v0 = 0;
   R.v1 = B.n;
   double* out = G + goff[T.blk] + (int64_t)T.i0 * K + T.j0;

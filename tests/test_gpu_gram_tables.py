@@ -1,6 +1,6 @@
-"""The Gram launch tables on both sides of the rule for their order (2,048 chunks: up to there in the
-order of the pairs, above dealt to the XCDs by second block), and made anew on one handle as the
-precision and the kind of blocks alternate, against the oracle.
+"""The Gram launch tables, dealt to the XCDs by second block, from a few chunks to more than run at
+once, and made anew on one handle as the precision and the kind of blocks alternate, against the
+oracle.
 
 Tolerances as for the widths: 1e-12 in FP64, 1e-5 in FP32, of the largest sum of |products|."""
 import dataclasses
