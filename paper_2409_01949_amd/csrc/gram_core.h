@@ -4,8 +4,8 @@
 // The points are `rows` runs of `len` consecutive points of both operands (one run where the
 // shared box is a whole block).  A run is read in loads of 8 or 16 bytes (GramLoad) whatever its
 // alignment, the last one masked; a stage is 128 bytes of every feature row in LDS, the next
-// stage's loads in registers meanwhile.  Row stride 144 bytes: the 16 rows x 4 vectors of a fragment read fall on every bank equally.  A
-// lane's fragment is one 16-byte LDS read, which feeds one 16-bit MFMA or several of the FP32
+// stage's loads in registers meanwhile.  Row stride 144 bytes: the 16 rows x 4 vectors of a fragment
+// read fall on every bank equally.  A lane's fragment is one 16-byte LDS read, which feeds one 16-bit MFMA or several of the FP32
 // and FP64 forms (k-slot lane/16 takes the lane's own points in turn: the same for X and Y).
 //
 // Four wavefronts: 2 x 2 squares of WT x WT tiles of 16 x 16, so a fragment serves WT products
@@ -36,7 +36,10 @@ constexpr int kGrStride = kGrVecs + 1; // and of an LDS row: one of padding
 // 11.3 ms, K = 48 0.54 against 0.72), FP32 entries by 4 (4.5 against 4.9 by 2 and 4.5 singly).
 // 16-bit entries on squares of 64 and 96 are loaded by 4 from the three dwords around them and cut
 // out: whole dwords are never split (K = 96 1.60 -> 1.54 ms, K = 48 120 -> 107 us, against 8-byte
-// and 16-byte loads where they lie); the other squares read 16 bytes (K = 256 73 against 80 us).
+// and 16-byte loads where they lie).  The other squares read 16 bytes: those of 128 lose by the cuts
+// (273 blocks of K = 100 / 128 / 160 / 256, all pairs: 247 / 325 / 808 / 1,213 us against 265 / 323 /
+// 895 / 1,234; only 11 blocks of K = 100 to 128 gain, 33 to 31), those of 32 are within 5% either way
+// (K = 8 39 against 42, K = 32 57 against 56).
 typedef uint32_t gr_half __attribute__((ext_vector_type(2)));
 template <int PREC, int WT> struct GramLoad { typedef gr_vec t; };
 template <int WT> struct GramLoad<ELMFB_FP64, WT> { typedef double t; };

@@ -92,7 +92,7 @@ __device__ __forceinline__ void l_envelope(const Geo& g, int l, int ix, int iy, 
 
 // One workgroup per tile of <= 256 points of one block; one thread per point, looping over K.
 // LO < 0: FP64 matrix only; LO = FP32 / BF16 / FP16: also its rounded copy.
-// Bound by instruction issue: 46 FP64 and about 30 other instructions an entry (25 of them the
+// Bound by instruction issue: 46 FP64 and about 30 other instructions an entry (26 of them the
 // tanh, 10 the operator; the 16-bit rounding 8).  The FP64 entries are streamed out (non-temporal:
 // the next pass over gigabytes finds nothing of them in the caches), the narrow copy is not (its
 // 2-byte lanes need the caches to merge lines: 719 us with the hint).  3-level problem with FP16

@@ -7,10 +7,10 @@
 // LDS and the lanes take their (block, feature) pairs 64 at a time, so no lane idles on a feature
 // count that is no multiple of 64.  The point's sum is reduced across the wavefront at the end in
 // a fixed order.  Bound by instruction issue: a tanh (the LDS table) and its loads per pair.
-// 230,400 points of the 3-level problem (19 blocks of K = 96 a point): 4,497 us with a serial
-// covering search in every lane and the device library's tanh, 1,116 us so; 9,216 points of the
-// L-shaped baseline (K = 16, where 48 of 64 lanes idled) 69 -> 16 us.  Held to 80 registers (6
-// wavefronts a SIMD for 4) it spills and takes 1,284 us.
+// Calls on 230,400 points of the 3-level problem (16 blocks of K = 96 a point): 4.30 ms with a
+// serial covering search in every lane and the device library's tanh, 0.99 ms so; 9,216 points of
+// the L-shaped baseline (K = 16, where 48 of 64 lanes idled) 69 -> 16 us.  Held to 80 registers (6
+// wavefronts a SIMD for 4) it spills and takes 15% longer.
 #include "device.h"
 #include "fast_tanh.h"
 #include "kernels.h"

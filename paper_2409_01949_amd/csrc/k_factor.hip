@@ -1,8 +1,9 @@
 // Block-Jacobi factors: for every block b the upper Cholesky factor R of G_b + lambda I (lambda =
 // shift trace(G_b)/K_b, G_b the diagonal Gram block) and X = R^{-1}, K_b <= 512 columns.
 //
-// One workgroup per block, blocked by panels of 32 rows on v_mfma_f64_16x16x4_f64, matrices K x K
-// row-major in global memory (G read only, R into W, X apart), the 16 rows being finished in LDS:
+// Blocks of up to 16 columns (24 in some launches, factor_by_width) take one wavefront each, in
+// registers: k_bj_factor_tile.  All others one workgroup per block (k_bj_factor), left-looking by
+// panels of 32 rows on v_mfma_f64_16x16x4_f64, matrices K x K row-major in global memory (G read only, R into W, X apart), the 16 rows being finished in LDS:
 //   R rows I:  S = G[I, J] - sum_{s < I} R[s, I]^T R[s, J]  (matrix cores, accumulators started at
 //              G, s ascending), then the 16 x 16 diagonal block in the registers of one wavefront
 //              (a column per lane, pivot rows by lane reads) and a column of S per thread by
@@ -14,13 +15,14 @@
 // caches deliver per CU.  Every entry's sum runs in the order of the unblocked elimination.
 //
 // Bound by the FP64 matrix rate, K^3/3 products a block, and by the 2 K/16 sequential 16-row steps,
-// which workgroups on one CU overlap: 128 registers a lane (four wavefronts a SIMD).  This file is
-// compiled at -O1: from -O2 on, value numbering keeps the unrolled steps' operands in registers
-// and the kernel takes 256 and spills.  Precondition calls, all kernels, -O3 at 256 registers / -O1
-// / -O1 at 128: 32 instances 8.0 / 6.5 / 6.0 ms, the same over 2 x 2 patches 40.9 / 39.2 / 36.8.
+// which workgroups on one CU overlap: at most 128 registers a lane (four wavefronts a SIMD; 124
+// and no spills to 256 columns, 34 spilled above).  This file is compiled at -O1: from -O2 on,
+// value numbering keeps the unrolled steps' operands in registers and the kernel takes 256 and
+// spills.  Precondition calls, all kernels, -O3 at 256 registers / -O1 / -O1 at 128: 32 instances
+// 8.0 / 6.5 / 6.0 ms, the same over 2 x 2 patches 40.9 / 39.2 / 36.8.
 // Against one column per thread and scalar updates, this kernel alone: 16 instances over 2 x 2
 // patches (K to 512) 28.1 -> 2.9 ms; 32 instances (blocks of K = 64 to 128, then in LDS with two
-// barriers a row) 4.5 -> 1.5 ms; 273 blocks of K = 96 1,119 -> 132 us.
+// barriers a row) 4.5 -> 1.3 ms; 273 blocks of K = 96 1,119 -> 125 us.
 //
 // A failed factorisation is retried with a 100x larger shift, 8 attempts in all; after that, or
 // for an all-zero block, the block gets the identity.

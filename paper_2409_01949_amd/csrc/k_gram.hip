@@ -21,11 +21,11 @@ namespace elmfb {
 // levels, follow each other on one XCD's L2 (by first block FP16 took 1.88 ms: 13 GB past the L2s
 // instead of 10.6; 8 or 40 groups an XCD instead of 16 1.62 and 1.61).  Staged before with one entry
 // per load, every feature row by every group of output tiles, chunks of 4,096 points whatever their
-// number; computations, before -> now:
-//   3-level problem, 5,361 pairs of K = 96: FP64 9.6 -> 8.5 ms (47 TFLOP/s), FP32 5.9 -> 4.5,
-//     FP16 3.3 -> 1.54 ms (260 TFLOP/s); its diagonal blocks 1,522 -> 750, 964 -> 422, 557 -> 202 us
-//   11 blocks of K = 256: 1,957 -> 480, 1,642 -> 257, 1,167 -> 73 us
-//   256 blocks of K = 16: 50 -> 20, 34 -> 14, 31 -> 11 us
+// number; computations with their chunk sums, before -> now:
+//   3-level problem, 5,361 pairs of K = 96: FP64 9.6 -> 8.8 ms (46 TFLOP/s), FP32 5.9 -> 4.6,
+//     FP16 3.3 -> 1.57 ms (255 TFLOP/s); its diagonal blocks 1,522 -> 725, 964 -> 424, 557 -> 201 us
+//   11 blocks of K = 256: 1,957 -> 440, 1,642 -> 254, 1,167 -> 82 us
+//   256 blocks of K = 16: 50 -> 18, 34 -> 13, 31 -> 10 us
 // (16 loads a row and stage instead of 8 take the registers of a wavefront a SIMD: FP64 8.7 -> 14 ms;
 // one contiguous range of chunks per XCD instead of dealt groups leaves the one with the coarse
 // blocks behind: FP16 2.3 -> 3.0 ms.)
